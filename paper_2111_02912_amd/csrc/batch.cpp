@@ -4,8 +4,9 @@
 // phases: their FFT passes on the streams, then one interpolation launch per
 // phase and kernel shape for all tasks (staged gathers of all forward-type
 // tasks of one dimension and window width, of all omega-Jacobian tasks, and
-// output-stationary spreads of all adjoint-type tasks with one owner-tile
-// shape), then each task's epilogue on its stream.
+// output-stationary spreads of the adjoint-type tasks with one owner-tile
+// shape; adjoint-type tasks on the matrix-core spread are issued whole), then
+// each task's epilogue on its stream.
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -141,7 +142,7 @@ bool same_group(const FuseGroup &g, const KbnPhased &ph) {
     const KbnGeom &x = ph.kind == 2 ? ph.sj.g : ph.gj.g;
     if (g.kind != ph.kind || g.D != x.D || g.J != x.J) return false;
     if (ph.kind != 2) return true;
-    if (g.sel.cpt != ph.sel.cpt || g.sel.ebv != ph.sel.ebv || g.sel.tcells != ph.sel.tcells) return false;
+    if (g.sel.cpt != ph.sel.cpt || g.sel.tcells != ph.sel.tcells) return false;
     for (int d = 0; d < x.D; ++d)
         if (g.To[d] != x.To[d]) return false;
     return true;
@@ -214,7 +215,6 @@ int prepare_phases(kbn_batch b, hipStream_t s) {
             std::vector<int> start(nm + 1, 0);
             for (int k = 0; k < nm; ++k) start[k + 1] = start[k] + jobs[k].ny;
             g.total = start[nm];
-            g.lds = g.sel.lds;
             host.resize(sizeof(KbnSpreadJob) * nm + sizeof(int) * (nm + 1));
             std::memcpy(host.data(), jobs.data(), sizeof(KbnSpreadJob) * nm);
             std::memcpy(host.data() + sizeof(KbnSpreadJob) * nm, start.data(), sizeof(int) * (nm + 1));
@@ -253,7 +253,7 @@ int launch_group(const FuseGroup &g, hipStream_t s) {
     } else {
         const KbnSpreadJob *jobs = (const KbnSpreadJob *)g.dev;
         const int *start = (const int *)(g.dev + sizeof(KbnSpreadJob) * nm);
-        e = kbn_launch_spread_os_multi(g.sel, g.D, g.J, g.maxngr, jobs, start, nm, (int)g.total, s);
+        e = kbn_launch_spread_os_multi(g.sel, g.J, g.maxngr, jobs, start, nm, (int)g.total, s);
     }
     if (e != hipSuccess) return kbn_internal_fail(KBN_ERR_HIP, hipGetErrorString(e));
     return KBN_OK;

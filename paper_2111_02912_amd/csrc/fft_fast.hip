@@ -712,17 +712,6 @@ constexpr int col_nt(int L) {
                          : KBN_BLOCK;
 }
 
-// workgroups of a kernel that can be resident on the current device at once
-template <class K>
-int64_t resident_blocks(K kernel, int nt, size_t lds) {
-    int nb = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, nt, lds) != hipSuccess || nb < 1) nb = 1;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 1;
-    return (int64_t)nb * cus;
-}
-
 // column passes that load ahead (L = 512: 0.65 -> 0.45 ms forward, 0.22 ->
 // 0.19 ms inverse for 256 images of 512 x 512 on MI355X; 128 and 256: 3-8%);
 // the longer lengths keep more elements per thread and would spill
@@ -744,7 +733,7 @@ hipError_t launch_cols_fwd(const KbnMidPassArgs &a, const float2 *tw, int64_t to
     if constexpr (col_pf(L)) {
         static const hipError_t ok = allow_lds(k_cols_pf<L, E, false, NT, DER, HALF>, LDS);
         if (ok != hipSuccess) return ok;
-        static const int64_t cap = resident_blocks(k_cols_pf<L, E, false, NT, DER, HALF>, NT, LDS);
+        static const int64_t cap = kbn_resident_blocks(k_cols_pf<L, E, false, NT, DER, HALF>, NT, LDS);
         k_cols_pf<L, E, false, NT, DER, HALF><<<dim3((unsigned)std::min<int64_t>(total, cap)), dim3(NT), LDS, s>>>(a, tw);
     } else {
         static const hipError_t ok = allow_lds(k_cols<L, E, false, NT, DER, HALF>, LDS);
@@ -763,7 +752,7 @@ hipError_t launch_cols_inv(const KbnMidPassArgs &a, const float2 *tw, int64_t to
     if constexpr (col_pf(L)) {
         static const hipError_t ok = allow_lds(k_cols_pf<L, E, true, NT>, LDS);
         if (ok != hipSuccess) return ok;
-        static const int64_t cap = resident_blocks(k_cols_pf<L, E, true, NT>, NT, LDS);
+        static const int64_t cap = kbn_resident_blocks(k_cols_pf<L, E, true, NT>, NT, LDS);
         k_cols_pf<L, E, true, NT><<<dim3((unsigned)std::min<int64_t>(total, cap)), dim3(NT), LDS, s>>>(a, tw);
     } else {
         static const hipError_t ok = allow_lds(k_cols<L, E, true, NT>, LDS);

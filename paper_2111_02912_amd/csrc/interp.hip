@@ -16,7 +16,7 @@
 //
 // spread (type 1, adjoint operator): each workgroup owns one tile of the
 // grid for a group of channels and sums every sample whose taps reach the
-// tile (see k_spread_os), then writes the tile with plain stores: every grid
+// tile (see k_spread_mf2), then writes the tile with plain stores: every grid
 // cell is written exactly once, so the grid needs neither zero-initialisation
 // nor atomics.
 #include "kbn_internal.h"
@@ -451,8 +451,8 @@ __global__ void __launch_bounds__(KBN_BLOCK) k_spread(KbnGeom g, KbnSpreadArgs a
         for (int d = D - 1; d >= 0; --d) {
             const int tc = rem % g.nto[d];
             rem /= g.nto[d];
-            a0[d] = tc * g.To[d];
-            te[d] = min(g.To[d], g.K[d] - a0[d]);
+            a0[d] = own_lo(tc, g.K[d], g.nto[d]);
+            te[d] = own_lo(tc + 1, g.K[d], g.nto[d]) - a0[d];
             pt[d] = acc_pitch(d, te[d]);
         }
     }
@@ -493,9 +493,10 @@ __global__ void __launch_bounds__(KBN_BLOCK) k_spread(KbnGeom g, KbnSpreadArgs a
             ent_p[t] = a.rec_p[e];
 #pragma unroll
             for (int d = 0; d < D; ++d) {
-                const int l = a.rec_l[(int64_t)e * D + d];
+                const int2 tr = a.rec_t[(int64_t)e * D + d];
+                const int l = tr.x;
                 float w[J];
-                kb_weights<J>(a.rec_f[(int64_t)e * D + d], g.coef, w);
+                kb_weights<J>(__int_as_float(tr.y), g.coef, w);
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
                     int loc = l + j;
@@ -596,41 +597,30 @@ __global__ void __launch_bounds__(KBN_BLOCK) k_spread(KbnGeom g, KbnSpreadArgs a
     }
 }
 
-// Output-stationary spread.  Workgroup = (work item of one owner tile,
-// group of CPT channels); one thread per cell of the tile (To^D threads), which
-// keeps the CPT channel sums of its cell in registers.  The work item's list
-// entries are staged in batches: per entry the tap origin relative to the
-// tile, the window weights of each axis (evaluated once per entry) and the
-// k-space values of the channel group.  Then every thread walks the batch: its
-// tap index per axis is its cell minus the entry's origin (mod K), its weight
-// the product of the axis weights (zero outside the J^D footprint), and it adds
-// weight * y into its sums.  No thread ever writes another thread's cell, so
-// there are no atomics and no read-modify-write of shared memory, and the sum
-// order (list order) is fixed.  The tile is written once at the end, to the
-// grid or to the work item's partial slot.
+// Output-stationary spread of 2D owner tiles of more than 8 cells per axis (a
+// caller's spread_tile).  Workgroup = (work item of one owner tile, group of CPT
+// channels); one thread per cell of the tile, which keeps the CPT channel sums
+// of its cell in registers.  The work item's list entries are staged in
+// batches: per entry the tap origin relative to the tile, the window weights
+// of each axis (evaluated once per entry) and the k-space values of the
+// channel group.  Then every thread walks the batch: its tap index per axis is
+// its cell minus the entry's origin (mod K), its weight the product of the
+// axis weights (zero outside the J^2 footprint), and it adds weight * y into
+// its sums.  No thread ever writes another thread's cell, so there are no
+// atomics and no read-modify-write of shared memory, and the sum order (list
+// order) is fixed.  The tile is written once at the end, to the grid or to the
+// work item's partial slot.
 // Body of one workgroup: channel group gx, work items wy, wy + ny, ...
 // (the kernel's blockIdx.x, blockIdx.y and gridDim.y).
-template <int D, int J, int CPT, int EB>
+template <int J, int CPT, int EB>
 __device__ __forceinline__ void spread_os_wg(const KbnGeom &g, const KbnSpreadArgs &a, int gx, int wy, int ny) {
+    constexpr int D = 2;
     __shared__ float2 s_y[EB][CPT];
     __shared__ int s_p[EB];
-    // 2D: per staged entry the tap origin relative to the tile and the J
-    // window weights of each axis.  3D: per staged entry and axis, the
-    // window weight seen by each cell coordinate of the tile along that axis
-    // (zero outside the footprint), so that a thread's weight is a product
-    // of table reads (measured faster in 3D, slower in 2D).
-    __shared__ float s_w[D == 2 ? EB : 1][D][J];
-    __shared__ int s_l[D == 2 ? EB : 1][D];
-    extern __shared__ float s_t[];  // 3D: [EB][D][To_max]
-    // 3D: the window polynomials' coefficients, read by every table entry
-    __shared__ float s_cf[D == 3 ? KBN_MAX_J * KBN_NCOEF : 1];
+    __shared__ float s_w[EB][D][J];
+    __shared__ int s_l[EB][D];
     const int nwork = a.scounts[0];
     const int nthr = blockDim.x;
-    if (D == 3)
-        for (int i = threadIdx.x; i < J * KBN_NCOEF; i += nthr) s_cf[i] = g.coef[i];  // seen after the first barrier
-    int tmax = 1;
-#pragma unroll
-    for (int d = 0; d < D; ++d) tmax = max(tmax, g.To[d]);
     int c[D];
     {
         int t = threadIdx.x;
@@ -642,8 +632,6 @@ __device__ __forceinline__ void spread_os_wg(const KbnGeom &g, const KbnSpreadAr
     }
     const int ch0 = gx * CPT;
     const int nchg = min(CPT, a.nch - ch0);
-    // 3D tiles of 8 x 8 cells per x-slice: a wave holds exactly one slice
-    const bool slice_waves = D == 3 && EB <= 64 && CPT <= 16 && g.To[1] == 8 && g.To[D - 1] == 8;
     // work items in dispatch order (hottest tiles first); a grid smaller
     // than the work list strides over it
     for (int wk = wy; wk < nwork; wk += ny) {
@@ -656,8 +644,8 @@ __device__ __forceinline__ void spread_os_wg(const KbnGeom &g, const KbnSpreadAr
             for (int d = D - 1; d >= 0; --d) {
                 const int tc = rem % g.nto[d];
                 rem /= g.nto[d];
-                a0[d] = tc * g.To[d];
-                te[d] = min(g.To[d], g.K[d] - a0[d]);
+                a0[d] = own_lo(tc, g.K[d], g.nto[d]);
+                te[d] = own_lo(tc + 1, g.K[d], g.nto[d]) - a0[d];
             }
         }
         bool active = true;
@@ -672,36 +660,15 @@ __device__ __forceinline__ void spread_os_wg(const KbnGeom &g, const KbnSpreadAr
             __syncthreads();  // previous batch (or work item) consumed
             for (int t = threadIdx.x; t < n; t += nthr) {
                 s_p[t] = a.rec_q[eb + t];
-                if (D == 2) {
 #pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        s_l[t][d] = a.rec_l[(int64_t)(eb + t) * D + d];
-                        float w[J];
-                        kb_weights<J>(a.rec_f[(int64_t)(eb + t) * D + d], g.coef, w);
+                for (int d = 0; d < D; ++d) {
+                    const int2 tr = a.rec_t[(int64_t)(eb + t) * D + d];
+                    s_l[t][d] = tr.x;
+                    float w[J];
+                    kb_weights<J>(__int_as_float(tr.y), g.coef, w);
 #pragma unroll
-                        for (int j = 0; j < J; ++j) s_w[t][d][j] = w[j];
-                    }
+                    for (int j = 0; j < J; ++j) s_w[t][d][j] = w[j];
                 }
-            }
-            // 3D weight tables: entry t, axis d, cell coordinate cc
-            for (int idx = threadIdx.x; D == 3 && idx < n * D * tmax; idx += nthr) {
-                const int cc = idx % tmax;
-                const int td = idx / tmax;
-                const int d = td % D;
-                const int t = td / D;
-                const int64_t e = eb + t;
-                int j = cc - a.rec_l[e * D + d];
-                if (j < 0) j += g.K[d];
-                float wv = 0.f;
-                if (j < J) {
-                    const float x = 2.f * a.rec_f[e * D + d] - 1.f;
-                    const float *cf = s_cf + j * KBN_NCOEF;
-                    float acc_w = cf[KBN_NCOEF - 1];
-#pragma unroll
-                    for (int k = KBN_NCOEF - 2; k >= 0; --k) acc_w = fmaf(acc_w, x, cf[k]);
-                    wv = acc_w;
-                }
-                s_t[idx] = wv;
             }
             __syncthreads();
             // loads past the batch or the channel group re-read a valid
@@ -715,73 +682,17 @@ __device__ __forceinline__ void spread_os_wg(const KbnGeom &g, const KbnSpreadAr
                 s_y[t][k] = a.y[(int64_t)(ch0 + (ok ? k : 0)) * a.M + (ok ? s_p[t] : 0)];
             }
             __syncthreads();
-            if (D == 3 && slice_waves) {
-                // The wave's entries: a ballot over the batch of the slice
-                // weights (lane t: entry t), so that the walk below visits
-                // only entries that reach the slice, KBN_SPREAD_OS_U at a time, with all
-                // their table and value reads issued before the sums.  The
-                // products and the order of the sums are those of the loop
-                // below.
-                const int t = threadIdx.x & 63;
-                const float wx_t = t < n ? s_t[t * D * tmax + c[0]] : 0.f;
-                unsigned long long todo = __ballot(wx_t != 0.f);
-                constexpr int U = KBN_SPREAD_OS_U;  // entries per step
-                while (todo) {
-                    int idx[U];
-                    bool has[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        has[u] = todo != 0;
-                        idx[u] = has[u] ? __builtin_ctzll(todo) : idx[0];
-                        if (has[u]) todo &= todo - 1;
-                    }
-                    float wv[U];
-                    float2 yv[U][CPT];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const float *ti = s_t + idx[u] * D * tmax;
-                        float w = ti[c[0]];
-#pragma unroll
-                        for (int d = 1; d < D; ++d) w *= ti[d * tmax + c[d]];
-                        wv[u] = w;
-#pragma unroll
-                        for (int k = 0; k < CPT; ++k) yv[u][k] = s_y[idx[u]][k];
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        if (!has[u]) break;
-#pragma unroll
-                        for (int k = 0; k < CPT; ++k) {
-                            acc[k].x = fmaf(wv[u], yv[u][k].x, acc[k].x);
-                            acc[k].y = fmaf(wv[u], yv[u][k].y, acc[k].y);
-                        }
-                    }
-                }
-                continue;
-            }
             for (int i = 0; i < n; ++i) {
-                float w;
-                if (D == 3) {
-                    const float *ti = s_t + i * D * tmax;
-                    w = ti[c[0]];
-                    // with 8 x 8 cells per x-slice a wave holds one slice, so
-                    // this skip is taken by whole waves when the footprint
-                    // misses the slice
-                    if (w == 0.f) continue;
+                float w = 1.f;
+                bool in = true;
 #pragma unroll
-                    for (int d = 1; d < D; ++d) w *= ti[d * tmax + c[d]];
-                } else {
-                    bool in = true;
-                    w = 1.f;
-#pragma unroll
-                    for (int d = 0; d < D; ++d) {
-                        int j = c[d] - s_l[i][d];
-                        if (j < 0) j += g.K[d];
-                        in = in && j < J;
-                        w *= s_w[i][d][j < J ? j : J - 1];
-                    }
-                    w = in ? w : 0.f;
+                for (int d = 0; d < D; ++d) {
+                    int j = c[d] - s_l[i][d];
+                    if (j < 0) j += g.K[d];
+                    in = in && j < J;
+                    w *= s_w[i][d][j < J ? j : J - 1];
                 }
+                w = in ? w : 0.f;
 #pragma unroll
                 for (int k = 0; k < CPT; ++k) {
                     const float2 y = s_y[i][k];
@@ -814,16 +725,16 @@ __device__ __forceinline__ void spread_os_wg(const KbnGeom &g, const KbnSpreadAr
     }
 }
 
-template <int D, int J, int CPT, int EB>
+template <int J, int CPT>
 __global__ void __launch_bounds__(512) k_spread_os(KbnGeom g, KbnSpreadArgs a) {
-    spread_os_wg<D, J, CPT, EB>(g, a, blockIdx.x, blockIdx.y, gridDim.y);
+    spread_os_wg<J, CPT, 32>(g, a, blockIdx.x, blockIdx.y, gridDim.y);
 }
 
 // The output-stationary spreads of several plans in one launch (same
 // owner-tile shape, so one workgroup size): workgroup row y belongs to the
 // job i with ystart[i] <= y < ystart[i + 1], which strides over its work
 // items with ny rows; columns past the job's channel groups stop at once.
-template <int D, int J, int CPT, int EB>
+template <int J, int CPT>
 __global__ void __launch_bounds__(512)
 k_spread_os_multi(const KbnSpreadJob *__restrict__ jobs, const int *__restrict__ ystart, int njobs) {
     const int y = blockIdx.y;
@@ -835,171 +746,388 @@ k_spread_os_multi(const KbnSpreadJob *__restrict__ jobs, const int *__restrict__
     }
     const KbnSpreadJob &j = jobs[lo];
     if ((int)blockIdx.x >= j.ngr) return;
-    spread_os_wg<D, J, CPT, EB>(j.g, j.a, blockIdx.x, y - ystart[lo], j.ny);
+    spread_os_wg<J, CPT, 32>(j.g, j.a, blockIdx.x, y - ystart[lo], j.ny);
 }
 
-// Output-stationary spread with one channel per lane, for 2D 8 x 8 owner
-// tiles and at least 64 channels.  A wave owns one tile for 64 channels and
-// each lane keeps the 64 cell sums of its own channel in registers.  Per
-// staged list entry the lanes share the window weights of each axis,
-// tabulated over the tile's 8 cell coordinates (zero outside the footprint),
-// and a mask of the rows the footprint covers; the wave visits only the
-// covered rows, with wave-uniform branches, and each lane adds weight * y of
-// its channel to the row's cells (a zero weight adds +0 outside the
-// footprint).  A cell's weight is the same product w_axis0 * w_axis1 as in
-// k_spread_os and the entries are added in list order, so both kernels
-// produce the same sums for finite data.  The finished tile goes
-// through LDS two rows at a time, so that each store instruction writes whole
-// row segments of a few channels instead of one cell of 64 channels.
-template <int J, int EB>
-__global__ void __launch_bounds__(64, KBN_SPREAD_CL_WAVES) k_spread_cl(KbnGeom g, KbnSpreadArgs a) {
-    constexpr int T = 8;
-    constexpr int NC = 64;         // channels per wave (one per lane)
-    constexpr int YP = NC + 1;     // padded entry row of the staged values
-    constexpr int TP = 2 * T + 1;  // padded channel row of two transposed tile rows
-    constexpr int SY = EB * YP > NC * TP ? EB * YP : NC * TP;
-    __shared__ float2 s_y[SY];
-    __shared__ float4 s_w[EB][2][T / 4];
-    __shared__ int s_m[EB];  // bit r: row r covered
-    __shared__ int s_p[EB];
-    // window polynomial coefficients of each tap, padded to 12 for float4
-    // reads (read from a global table, the compiler keeps all 66 in vector
-    // registers next to the 128 of the sums)
-    constexpr int CP = 12;
-    static_assert(KBN_NCOEF <= CP, "coefficient padding");
-    static_assert(NC % EB == 0 && (EB * 2 * T) % NC == 0, "batch size");
-    __shared__ float4 s_coef[J * CP / 4];
-    const int lane = threadIdx.x;
-    for (int i = lane; i < J * CP; i += NC) {
-        const int j = i / CP, k = i - j * CP;
-        reinterpret_cast<float *>(s_coef)[i] = k < KBN_NCOEF ? g.coef[j * KBN_NCOEF + k] : 0.f;
-    }
-    const int ch0 = blockIdx.x * NC;
-    const int nchg = min(NC, a.nch - ch0);
+// Output-stationary spread on the matrix cores, for owner tiles of at most 8
+// cells per axis.  The tile's sums are the contraction
+//   tile[channel, cell] = sum_entries y[entry, channel] * w[entry, cell],
+// and v_mfma_f32_16x16x4_f32 takes four list entries per instruction: A holds
+// 16 reals of y (8 channels), B the weights of 16 cells, and the 64 cells of
+// an 8 x 8 tile (in 3D: of one x-slice) are four instructions.  One FP32
+// matrix instruction adds its four products as a chain of four FMAs in entry
+// order, so a cell's sum is the one that an FMA loop over the list would
+// form; entries of zero weight and the padding of the last four (value and
+// weight zero) leave it unchanged.  Hence the sums do not depend on how the
+// channels are grouped.
+//
+// A batch of entries is staged in LDS, one record per entry: the window
+// weights seen by the 8 cell coordinates of each axis (zero outside the
+// footprint; every lane evaluates the polynomial of one tap, coefficients in
+// registers, and a cross-lane read moves tap to cell) and the channels' values.
+// Records past the end are zero.  The next batch's loads are in flight
+// while the matrix cores work on the current one (two LDS buffers, one
+// barrier per batch).
+//
+// FP32 matrix instructions share the SIMD's FMA units (measured: their 32
+// cycles and the VALU's 4 per instruction add up), so both count: 96^3 x 8
+// coils (kooshball, 1M samples) issues 17.5M matrix and 116M vector
+// instructions, 1.0M of its 1.35M cycles per SIMD.  Measured against the
+// cell-per-lane kernels it replaces: that adjoint's spread 1482 -> 600 us
+// (plus 44 us for the copy in tile order), 75 x 90 x 64 x 4 coils 509 -> 73 us,
+// 384^2 x 8 coils 60 -> 29 us, 320^2 x 64 channels 118 -> 64 us, 256^2 x 256
+// channels (whose 0.54 GB of grid take 0.1 ms to write) 235 -> 194 us.
+// Measured and not kept: one autonomous wave per item without staging
+// (927 us at 96^3, the weights evaluated per slice), workgroups that stay
+// resident and load across items (744 us: static shares), batches sorted by
+// slice so that a wave could own all slices (693-920 us).
+typedef float mf_f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ mf_f4 mfma4(float a, float b, mf_f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// tap polynomial of fraction f with this lane's coefficients
+__device__ __forceinline__ float tap_poly(const float (&cf)[KBN_NCOEF], float f) {
+    const float x = 2.f * f - 1.f;
+    float w = cf[KBN_NCOEF - 1];
+#pragma unroll
+    for (int k = KBN_NCOEF - 2; k >= 0; --k) w = fmaf(w, x, cf[k]);
+    return w;
+}
+
+// From the tap values w (tap = lane & 7) of an axis with K cells whose first
+// tap sits at cell `rel` of the tile (modulo K): the weight of tile cell c,
+// zero outside the footprint or when !ok.
+template <int J>
+__device__ __forceinline__ float cell_weight(float w, int rel, int c, int K, bool ok) {
+    int j = c - rel;
+    if (j < 0) j += K;
+    const int src = ((int)threadIdx.x & 56) + (j & 7);
+    const float v = __int_as_float(__builtin_amdgcn_ds_bpermute(src * 4, __float_as_int(w)));
+    return ok && j < J ? v : 0.f;
+}
+
+template <int J>
+__device__ __forceinline__ void lane_coefs(const float *__restrict__ coef, float (&cf)[KBN_NCOEF]) {
+    const int tap = threadIdx.x & 7;
+#pragma unroll
+    for (int k = 0; k < KBN_NCOEF; ++k) cf[k] = tap < J ? coef[tap * KBN_NCOEF + k] : 0.f;
+}
+
+// 2D: a workgroup of four waves per (work item, 32 / CS * NG channels).  CS
+// waves share the tile's four 2-row blocks and 4 / CS take different
+// channels, 8 * NG each.
+template <int J, int CS, int NG>
+__global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5) k_spread_mf2(KbnGeom g, KbnSpreadArgs a) {
+    constexpr int CHW = 32 / CS * NG;                          // channels per workgroup
+    constexpr int BW = 4 / CS;                                 // blocks per wave
+    constexpr int EB = CHW <= 8 ? 64 : (CHW <= 32 ? 32 : 16);  // entries per batch
+    constexpr int YF = EB * CHW / 256;                         // values per thread and batch
+    constexpr int TP = EB / 16;                                // weight passes (16 entries x 2 axes)
+    // floats per record: rows (even cells, then odd), columns, values; 16 or
+    // 48 modulo 64, so that four consecutive records' values take all banks
+    constexpr int STR = CHW == 8 ? 48 : 16 + 2 * CHW;
+    __shared__ __align__(16) float rec[2][EB * STR];
+    const int tid = threadIdx.x, lane = tid & 63, k = lane >> 4, i = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wch = wv / CS, wcell = wv % CS;  // this wave's channels and blocks
+    float cf[KBN_NCOEF];
+    lane_coefs<J>(g.coef, cf);
+    const int ch0 = blockIdx.x * CHW;
+    const int nchg = min(CHW, a.nch - ch0);
+    // staging: weights of (entry te + 16 pass, axis ax, cell cc), values of
+    // (entry ty, channels kb + 256 / EB r)
+    const int te = tid >> 4, ax = (tid >> 3) & 1, cc = tid & 7;
+    const int ty = tid % EB, kb = tid / EB;
+    const int Kx = ax ? g.K[1] : g.K[0];
+    const int wpos = ax ? 8 + cc : (cc & 1) * 4 + (cc >> 1);
+    const float2 *yb[YF];
+#pragma unroll
+    for (int r = 0; r < YF; ++r) yb[r] = a.y + (int64_t)(ch0 + min(kb + 256 / EB * r, nchg - 1)) * a.M;
     const int nwork = a.scounts[0];
-    for (int wk = blockIdx.y; wk < nwork; wk += gridDim.y) {
-        const int tile = a.swork[4 * wk];
-        const int slot = a.swork[4 * wk + 3];
-        const int e0 = a.swork[4 * wk + 1], e1 = a.swork[4 * wk + 2];
-        const int tr = tile / g.nto[1];
-        const int a0r = tr * T, a0c = (tile - tr * g.nto[1]) * T;
-        const int ter = min(T, g.K[0] - a0r), tec = min(T, g.K[1] - a0c);
-        float2 acc[T][T];
+    int wk = blockIdx.y;
+    int4 item = reinterpret_cast<const int4 *>(a.swork)[wk];  // tile, first entry, end, slot
+    int q = 0;
+    int2 t[TP];
+    float2 yv[YF];
+    // loads of the n entries from eb on; lanes past them repeat the last one,
+    // so that all loads are issued without branches (stage writes zeros there)
+    auto index = [&](int eb, int n) {
+        if (n > 0) q = a.rec_q[eb + min(ty, n - 1)];
+    };
+    auto fetch = [&](int eb, int n) {
 #pragma unroll
-        for (int r = 0; r < T; ++r)
+        for (int r = 0; r < YF; ++r) yv[r] = yb[r][q];
+        const int2 *tb = a.rec_t + 2 * (int64_t)eb + ax;
 #pragma unroll
-            for (int c = 0; c < T; ++c) acc[r][c] = make_float2(0.f, 0.f);
-        for (int eb = e0; eb < e1; eb += EB) {
-            const int n = min(EB, e1 - eb);
-            __syncthreads();  // previous batch (or tile write-out) consumed
-            if (lane < n) s_p[lane] = a.rec_q[eb + lane];
-            // window weights: lane -> (entry t, axis d, cell cc), EB * 16
-            // cells in passes of 64, each the tap polynomial of its cell with
-            // the Horner steps of kb_weights; the row masks come from a
-            // ballot over the axis-0 cells of each entry
+        for (int p = 0; p < TP; ++p) t[p] = tb[2 * min(te + 16 * p, n - 1)];
+    };
+    auto stage = [&](float *buf, int n) {
 #pragma unroll
-            for (int it = 0; it < EB * 2 * T / NC; ++it) {
-                const int idx = it * NC + lane;
-                const int t = idx / (2 * T), d = (idx / T) & 1, cc = idx % T;
-                bool in = false;
-                float wv = 0.f;
-                if (t < n) {
-                    const int64_t e = eb + t;
-                    int j = cc - a.rec_l[e * 2 + d];
-                    if (j < 0) j += g.K[d];
-                    in = j < J && cc < (d == 0 ? ter : tec);
-                    const float x = 2.f * a.rec_f[e * 2 + d] - 1.f;
-                    const int jc = in ? j : 0;
-                    float cf[CP];
+        for (int p = 0; p < TP; ++p)
+            buf[(te + 16 * p) * STR + wpos] =
+                cell_weight<J>(tap_poly(cf, __int_as_float(t[p].y)), t[p].x, cc, Kx, te + 16 * p < n);
 #pragma unroll
-                    for (int q = 0; q < CP / 4; ++q) {
-                        const float4 c4 = s_coef[jc * (CP / 4) + q];
-                        cf[4 * q] = c4.x, cf[4 * q + 1] = c4.y, cf[4 * q + 2] = c4.z, cf[4 * q + 3] = c4.w;
-                    }
-                    float acc_w = cf[KBN_NCOEF - 1];
+        for (int r = 0; r < YF; ++r)
+            *reinterpret_cast<float2 *>(buf + ty * STR + 16 + 2 * (kb + 256 / EB * r)) =
+                ty < n ? yv[r] : make_float2(0.f, 0.f);
+    };
+    for (; wk < nwork; wk += gridDim.y) {
+        if (wk != (int)blockIdx.y) item = reinterpret_cast<const int4 *>(a.swork)[wk];
+        const int e0 = item.y, e1 = item.z;
+        mf_f4 acc[NG][BW];
 #pragma unroll
-                    for (int k = KBN_NCOEF - 2; k >= 0; --k) acc_w = fmaf(acc_w, x, cf[k]);
-                    wv = in ? acc_w : 0.f;
-                }
-                reinterpret_cast<float *>(s_w)[idx] = wv;
-                const unsigned long long bal = __ballot(in);
-                if ((lane & (2 * T - 1)) == 0) s_m[t] = (int)((bal >> (lane & ~(2 * T - 1))) & 0xFF);
+        for (int n = 0; n < NG; ++n)
+#pragma unroll
+            for (int b = 0; b < BW; ++b) acc[n][b] = mf_f4{0.f, 0.f, 0.f, 0.f};
+        if (e0 < e1) {
+            index(e0, e1 - e0);
+            fetch(e0, e1 - e0);
+            index(e0 + EB, e1 - e0 - EB);
+            stage(rec[0], e1 - e0);
+        }
+        lds_barrier();
+        int cur = 0;
+        for (int eb = e0; eb < e1; eb += EB, cur ^= 1) {
+            const bool more = eb + EB < e1;
+            if (more) {
+                fetch(eb + EB, e1 - eb - EB);
+                index(eb + 2 * EB, e1 - eb - 2 * EB);
             }
-            __syncthreads();
-            // values: 64 channels x EB entries, entries fastest (consecutive
-            // list entries are mostly consecutive samples); a lane keeps one
-            // entry and steps over channels.  Loads past the batch or the
-            // channel count re-read a valid value, so that all are issued
-            // without branches and are in flight together; their addresses
-            // are 32-bit byte offsets from the group's first channel (the
-            // host takes this kernel only when 64 channels of k-space span
-            // less than 2 GiB).
-            {
-                constexpr int KS = NC / EB;  // channels per load round
-                const int t = lane % EB, kb = lane / EB;
-                const int q = t < n ? s_p[t] : 0;
-                const char *base = reinterpret_cast<const char *>(a.y + (int64_t)ch0 * a.M);
-                const unsigned cs = (unsigned)a.M * 8u;  // bytes per channel
-                float2 v[EB];
+            const float *buf = rec[cur] + k * STR;
+            const int nst = (min(EB, e1 - eb) + 3) / 4;
+            for (int s = 0; s < nst; ++s) {
+                const float *rs = buf + 4 * s * STR;
+                const float wc = rs[8 + (i & 7)];
+                float w[BW], v[NG];
 #pragma unroll
-                for (int r = 0; r < EB; ++r) {
-                    const unsigned k = (unsigned)min(kb + KS * r, nchg - 1);
-                    v[r] = *reinterpret_cast<const float2 *>(base + ((unsigned)q * 8u + k * cs));
-                }
+                for (int b = 0; b < BW; ++b) w[b] = rs[(i >> 3) * 4 + wcell * BW + b] * wc;
 #pragma unroll
-                for (int r = 0; r < EB; ++r) s_y[t * YP + kb + KS * r] = v[r];
+                for (int n = 0; n < NG; ++n) v[n] = rs[16 + (wch * NG + n) * 16 + i];
+#pragma unroll
+                for (int n = 0; n < NG; ++n)
+#pragma unroll
+                    for (int b = 0; b < BW; ++b) acc[n][b] = mfma4(v[n], w[b], acc[n][b]);
             }
-            __syncthreads();
-            for (int i = 0; i < n; ++i) {
-                const float2 v = s_y[i * YP + lane];
-                const int m = __builtin_amdgcn_readfirstlane(s_m[i]);
-                float wr[T], wc[T];
+            if (more) stage(rec[cur ^ 1], e1 - eb - EB);
+            lds_barrier();
+        }
+        // lane: cell (row 2 b + i / 8, column i % 8) of channels 8 n + 2 k, + 1
+        const int tr = item.x / g.nto[1], tc = item.x - tr * g.nto[1];
+        const int a0r = own_lo(tr, g.K[0], g.nto[0]), a0c = own_lo(tc, g.K[1], g.nto[1]);
+        const int ter = own_lo(tr + 1, g.K[0], g.nto[0]) - a0r, tec = own_lo(tc + 1, g.K[1], g.nto[1]) - a0c;
+        float2 *dst;
+        int64_t cs;
+        int rs;  // channel and row strides
+        if (item.w >= 0) {
+            cs = (int64_t)g.To[0] * g.To[1];
+            rs = tec;
+            dst = a.partial + ((int64_t)item.w * a.nch + ch0) * cs;
+        } else {
+            cs = a.gsize;
+            rs = g.K[1];
+            dst = a.grid + (int64_t)ch0 * cs + (int64_t)a0r * rs + a0c;
+        }
 #pragma unroll
-                for (int q = 0; q < T / 4; ++q) {
-                    const float4 r4 = s_w[i][0][q], c4 = s_w[i][1][q];
-                    wr[4 * q] = r4.x, wr[4 * q + 1] = r4.y, wr[4 * q + 2] = r4.z, wr[4 * q + 3] = r4.w;
-                    wc[4 * q] = c4.x, wc[4 * q + 1] = c4.y, wc[4 * q + 2] = c4.z, wc[4 * q + 3] = c4.w;
+        for (int n = 0; n < NG; ++n)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = 8 * (wch * NG + n) + 2 * k + h;
+#pragma unroll
+                for (int b = 0; b < BW; ++b) {
+                    const int r = 2 * (wcell * BW + b) + (i >> 3);
+                    if (c < nchg && r < ter && (i & 7) < tec)
+                        dst[c * cs + r * rs + (i & 7)] = make_float2(acc[n][b][2 * h], acc[n][b][2 * h + 1]);
                 }
+            }
+    }
+}
+
+// k-space of each group of `cg` channels in tile order with the group's
+// channels side by side, so that one entry's values are one short read:
+// ys[group * cg * M + p * width + c] (width = channels of the group).
+__global__ void __launch_bounds__(KBN_BLOCK)
+k_permute_groups(const float2 *__restrict__ y, float2 *__restrict__ ys, const int *__restrict__ order, int64_t M,
+                 int nch, int cg) {
+    const int ch0 = blockIdx.y * cg;
+    const int w = min(cg, nch - ch0);
+    const int64_t i = (int64_t)blockIdx.x * KBN_BLOCK + threadIdx.x;
+    const int64_t p = i / w;
+    if (p >= M) return;
+    const int c = (int)(i - p * w);
+    ys[(int64_t)ch0 * M + i] = y[(int64_t)(ch0 + c) * M + order[p]];
+}
+
+// 3D: a workgroup of 8 / S * CS waves per (work item, 8 / S channels), each
+// wave taking S adjacent x-slices of the tile and, of their four 2-row blocks,
+// 4 / CS.  The 16 reals of A are the S slices x
+// 8 / S channels, A = w_x * y, and B = w_y * w_z over the 8 x 8 cells of a
+// slice, so that few channels still fill the operand.  Of each batch a wave
+// visits only the entries that reach its slices (a footprint covers 6 of the
+// 13 positions of its first tap around an 8-cell tile), through a list of
+// record offsets padded with the zero record.
+template <int J, int S, int CS>
+__global__ void __launch_bounds__(512 / S * CS, S == 2 ? 5 : 6) k_spread_mf3(KbnGeom g, KbnSpreadArgs a) {
+    constexpr int CG = 8 / S;             // channels per group
+    constexpr int W = 8 / S * CS;         // waves
+    constexpr int BW = 4 / CS;            // blocks per wave
+    constexpr int NT = 64 * W;            // threads
+    constexpr int EB = 64;                // entries per batch (one per lane)
+    constexpr int PE = EB * 8 / NT;       // weight passes per axis (NT / 8 entries each)
+    constexpr int YF = EB * CG > NT ? EB * CG / NT : 1;  // values per thread and batch
+    static_assert(PE >= 1, "batch shape");
+    // floats per record: y (even cells, then odd), z, x, values
+    constexpr int STR = 48;
+    __shared__ __align__(16) float rec[2][(EB + 1) * STR];
+    __shared__ int s_reach[2][EB];        // slices (bits) that each entry reaches
+    __shared__ int s_off[W][EB + 4];
+    const int tid = threadIdx.x, lane = tid & 63, k = lane >> 4, i = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sx = wv / CS * S;           // this wave's first slice
+    const int wcell = wv % CS;            // and its blocks
+    const int sub = i / (16 / S);         // slice of this lane's real
+    float cf[KBN_NCOEF];
+    lane_coefs<J>(g.coef, cf);
+    const int ch0 = blockIdx.x * CG;
+    const int nchg = min(CG, a.nch - ch0);
+    // staging: weights of (entry te + NT / 8 pass, axis, cell cc), values of
+    // (entry ty + NT / CG pass, channel yc)
+    const int te = tid >> 3, cc = tid & 7;
+    const int ty = tid / CG, yc = tid % CG;
+    const float2 *yb = a.ys + (int64_t)ch0 * a.M + min(yc, nchg - 1);
+    for (int x = tid; x < STR; x += NT) rec[0][EB * STR + x] = rec[1][EB * STR + x] = 0.f;
+    const int nwork = a.scounts[0];
+    int wk = blockIdx.y;
+    int4 item = reinterpret_cast<const int4 *>(a.swork)[wk];  // tile, first entry, end, slot
+    int q[YF];
+    int2 t[3 * PE];
+    float2 yv[YF];
+    // loads of the n entries from eb on; lanes past them repeat the last one,
+    // so that all loads are issued without branches (stage writes zeros there)
+    auto index = [&](int eb, int n) {
+        if (n > 0) {
 #pragma unroll
-                for (int r = 0; r < T; ++r) {
-                    if (m & (1 << r)) {
+            for (int r = 0; r < YF; ++r) q[r] = a.rec_p[eb + min(ty + NT / CG * r, n - 1)];
+        }
+    };
+    auto fetch = [&](int eb, int n) {
 #pragma unroll
-                        for (int c = 0; c < T; ++c) {
-                            const float w = wr[r] * wc[c];
-                            acc[r][c].x = fmaf(w, v.x, acc[r][c].x);
-                            acc[r][c].y = fmaf(w, v.y, acc[r][c].y);
-                        }
-                    }
-                }
+        for (int r = 0; r < YF; ++r) yv[r] = yb[(int64_t)q[r] * nchg];
+        const int2 *tb = a.rec_t + 3 * (int64_t)eb;
+#pragma unroll
+        for (int p = 0; p < 3 * PE; ++p) t[p] = tb[3 * min(te + NT / 8 * (p % PE), n - 1) + p / PE];
+    };
+    auto stage = [&](int b, int n) {
+        float *buf = rec[b];
+#pragma unroll
+        for (int p = 0; p < 3 * PE; ++p) {
+            const int e = te + NT / 8 * (p % PE);
+            const int x = p / PE;
+            const int pos = x == 0 ? 16 + cc : (x == 1 ? (cc & 1) * 4 + (cc >> 1) : 8 + cc);
+            const float w = cell_weight<J>(tap_poly(cf, __int_as_float(t[p].y)), t[p].x, cc, g.K[x], e < n);
+            buf[e * STR + pos] = w;
+            if (S < 8 && x == 0) {
+                const unsigned long long m = __ballot(w != 0.f);
+                if (cc == 0) s_reach[b][e] = (int)(m >> (lane & 56)) & 255;
             }
         }
 #pragma unroll
-        for (int r0 = 0; r0 < T; r0 += 2) {
-            __syncthreads();
+        for (int r = 0; r < YF; ++r)
+            if (ty + NT / CG * r < EB)
+                *reinterpret_cast<float2 *>(buf + (ty + NT / CG * r) * STR + 24 + 2 * yc) =
+                    ty + NT / CG * r < n ? yv[r] : make_float2(0.f, 0.f);
+    };
+    for (; wk < nwork; wk += gridDim.y) {
+        if (wk != (int)blockIdx.y) item = reinterpret_cast<const int4 *>(a.swork)[wk];
+        const int e0 = item.y, e1 = item.z;
+        mf_f4 acc[BW];
 #pragma unroll
-            for (int dr = 0; dr < 2; ++dr)
+        for (int b = 0; b < BW; ++b) acc[b] = mf_f4{0.f, 0.f, 0.f, 0.f};
+        if (e0 < e1) {
+            index(e0, e1 - e0);
+            fetch(e0, e1 - e0);
+            index(e0 + EB, e1 - e0 - EB);
+            stage(0, e1 - e0);
+        }
+        lds_barrier();
+        int cur = 0;
+        for (int eb = e0; eb < e1; eb += EB, cur ^= 1) {
+            const bool more = eb + EB < e1;
+            if (more) {
+                fetch(eb + EB, e1 - eb - EB);
+                index(eb + 2 * EB, e1 - eb - 2 * EB);
+            }
+            const float *buf = rec[cur];
+            int n = min(EB, e1 - eb);
+            if constexpr (S < 8) {
+                // the list is the wave's own: its LDS accesses complete in
+                // program order
+                const bool hit = ((s_reach[cur][lane] >> sx) & ((1 << S) - 1)) != 0;
+                const unsigned long long m = __ballot(hit);
+                if (hit) s_off[wv][__popcll(m & ((1ull << lane) - 1ull))] = lane * STR;
+                n = __popcll(m);
+                if (lane < 3) s_off[wv][n + lane] = EB * STR;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+                __builtin_amdgcn_wave_barrier();
+            }
+            const int nst = (n + 3) / 4;
+            // operands of one step, read a step ahead for S > 1 (two workgroups
+            // of S = 1 need the registers more: six waves per SIMD)
+            float wc, wx, v, wr[BW];
+            auto operands = [&](int s) {
+                const float *rs = buf + (S < 8 ? s_off[wv][4 * s + k] : (4 * s + k) * STR);
+                wc = rs[8 + (i & 7)];
+                wx = rs[16 + sx + sub];
+                v = rs[24 + i % (16 / S)];
 #pragma unroll
-                for (int c = 0; c < T; ++c) s_y[lane * TP + dr * T + c] = acc[r0 + dr][c];
-            __syncthreads();
-            // lane -> one cell of the two rows, stepping over channels
-            const int cell = lane % (2 * T), kb = lane / (2 * T);
-            constexpr int KS = NC / (2 * T);
-            const int r = r0 + cell / T, c = cell % T;
-            if (r < ter && c < tec) {
-                float2 *dst;
-                int64_t step;
-                if (slot >= 0) {
-                    dst = a.partial + ((int64_t)slot * a.nch + ch0 + kb) * (T * T) + r * tec + c;
-                    step = (int64_t)KS * T * T;
-                } else {
-                    dst = a.grid + (int64_t)(ch0 + kb) * a.gsize + (int64_t)(a0r + r) * g.K[1] + a0c + c;
-                    step = (int64_t)KS * a.gsize;
-                }
+                for (int b = 0; b < BW; ++b) wr[b] = rs[(i >> 3) * 4 + wcell * BW + b];
+            };
+            if (S > 1 && nst > 0) operands(0);
+            for (int s = 0; s < nst; ++s) {
+                if (S == 1) operands(s);
+                const float av = wx * v;
+                float w[BW];
 #pragma unroll
-                for (int it = 0; it < 2 * T; ++it) {
-                    const int k = kb + KS * it;
-                    if (k < nchg) dst[it * step] = s_y[k * TP + cell];
-                }
+                for (int b = 0; b < BW; ++b) w[b] = wr[b] * wc;
+                if (S > 1) operands(min(s + 1, nst - 1));
+#pragma unroll
+                for (int b = 0; b < BW; ++b) acc[b] = mfma4(av, w[b], acc[b]);
+            }
+            if (more) stage(cur ^ 1, e1 - eb - EB);
+            lds_barrier();
+        }
+        int a0[3], tn[3];
+        {
+            int rem = item.x;
+#pragma unroll
+            for (int x = 2; x >= 0; --x) {
+                const int o = rem % g.nto[x];
+                rem /= g.nto[x];
+                a0[x] = own_lo(o, g.K[x], g.nto[x]);
+                tn[x] = own_lo(o + 1, g.K[x], g.nto[x]) - a0[x];
+            }
+        }
+        // lane: cell (row 2 b + i / 8, column i % 8) of the two (slice, channel)
+        // pairs of accumulator reals 4 k .. 4 k + 3
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = 4 * k + 2 * h;
+            const int x = sx + r / (16 / S), c = (r % (16 / S)) >> 1;
+            if (c >= nchg || x >= tn[0] || (i & 7) >= tn[2]) continue;
+            float2 *dst;
+            int rs;
+            if (item.w >= 0) {
+                rs = tn[2];
+                dst = a.partial + ((int64_t)item.w * a.nch + ch0 + c) * (g.To[0] * g.To[1] * g.To[2]) + x * tn[1] * tn[2];
+            } else {
+                rs = g.K[2];
+                dst = a.grid + (int64_t)(ch0 + c) * a.gsize + ((int64_t)(a0[0] + x) * g.K[1] + a0[1]) * rs + a0[2];
+            }
+#pragma unroll
+            for (int b = 0; b < BW; ++b) {
+                const int y = 2 * (wcell * BW + b) + (i >> 3);
+                if (y < tn[1]) dst[y * rs + (i & 7)] = make_float2(acc[b][2 * h], acc[b][2 * h + 1]);
             }
         }
     }
@@ -1019,8 +1147,8 @@ __global__ void __launch_bounds__(KBN_BLOCK) k_spread_combine(KbnGeom g, KbnSpre
         for (int d = D - 1; d >= 0; --d) {
             const int tc = rem % g.nto[d];
             rem /= g.nto[d];
-            a0[d] = tc * g.To[d];
-            te[d] = min(g.To[d], g.K[d] - a0[d]);
+            a0[d] = own_lo(tc, g.K[d], g.nto[d]);
+            te[d] = own_lo(tc + 1, g.K[d], g.nto[d]) - a0[d];
         }
         int tsize = 1, pstride = 1;
         for (int d = 0; d < D; ++d) {
@@ -1029,10 +1157,19 @@ __global__ void __launch_bounds__(KBN_BLOCK) k_spread_combine(KbnGeom g, KbnSpre
         }
         for (int i = threadIdx.x; i < tsize; i += blockDim.x) {
             float2 sum = make_float2(0.f, 0.f);
-            for (int s = 0; s < ns; ++s) {
-                const float2 v = a.partial[((int64_t)(slot0 + s) * a.nch + ch) * pstride + i];
-                sum.x += v.x;
-                sum.y += v.y;
+            const float2 *part = a.partial + ((int64_t)slot0 * a.nch + ch) * pstride + i;
+            const int64_t step = (int64_t)a.nch * pstride;
+            for (int s = 0; s < ns; s += 8) {  // eight loads in flight, added in slot order
+                float2 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = part[min(s + u, ns - 1) * step];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    if (s + u < ns) {
+                        sum.x += v[u].x;
+                        sum.y += v[u].y;
+                    }
+                }
             }
             int r = i;
             int64_t off = 0, stride = 1;
@@ -1182,52 +1319,56 @@ SpreadShape spread_shape(const KbnGeom &g, int nch) {
     return sh;
 }
 
-template <int D, int J>
+template <int J>
 hipError_t launch_os(const KbnSpreadSel &sel, dim3 grid, const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
     const dim3 blk((unsigned)sel.tcells);
-    if constexpr (D == 3) {
-        switch (sel.cpt) {
-            case 1: k_spread_os<D, J, 1, 64><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 2: k_spread_os<D, J, 2, 64><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 4: k_spread_os<D, J, 4, 64><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 8: k_spread_os<D, J, 8, 64><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 16: k_spread_os<D, J, 16, 64><<<grid, blk, sel.lds, s>>>(g, a); break;
-            default: k_spread_os<D, J, 32, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-        }
-    } else {
-        switch (sel.cpt) {
-            case 1: k_spread_os<D, J, 1, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 2: k_spread_os<D, J, 2, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 4: k_spread_os<D, J, 4, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 8: k_spread_os<D, J, 8, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-            case 16: k_spread_os<D, J, 16, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-            default: k_spread_os<D, J, 32, 32><<<grid, blk, sel.lds, s>>>(g, a); break;
-        }
+    switch (sel.cpt) {
+        case 1: k_spread_os<J, 1><<<grid, blk, 0, s>>>(g, a); break;
+        case 2: k_spread_os<J, 2><<<grid, blk, 0, s>>>(g, a); break;
+        case 4: k_spread_os<J, 4><<<grid, blk, 0, s>>>(g, a); break;
+        case 8: k_spread_os<J, 8><<<grid, blk, 0, s>>>(g, a); break;
+        case 16: k_spread_os<J, 16><<<grid, blk, 0, s>>>(g, a); break;
+        default: k_spread_os<J, 32><<<grid, blk, 0, s>>>(g, a); break;
     }
     return hipGetLastError();
 }
 
-template <int D, int J>
+template <int J>
 hipError_t launch_os_multi(const KbnSpreadSel &sel, dim3 grid, const KbnSpreadJob *jobs, const int *ystart,
                            int njobs, hipStream_t s) {
     const dim3 blk((unsigned)sel.tcells);
-    if constexpr (D == 3) {
+    switch (sel.cpt) {
+        case 1: k_spread_os_multi<J, 1><<<grid, blk, 0, s>>>(jobs, ystart, njobs); break;
+        case 2: k_spread_os_multi<J, 2><<<grid, blk, 0, s>>>(jobs, ystart, njobs); break;
+        case 4: k_spread_os_multi<J, 4><<<grid, blk, 0, s>>>(jobs, ystart, njobs); break;
+        case 8: k_spread_os_multi<J, 8><<<grid, blk, 0, s>>>(jobs, ystart, njobs); break;
+        case 16: k_spread_os_multi<J, 16><<<grid, blk, 0, s>>>(jobs, ystart, njobs); break;
+        default: k_spread_os_multi<J, 32><<<grid, blk, 0, s>>>(jobs, ystart, njobs); break;
+    }
+    return hipGetLastError();
+}
+
+// the matrix-core spread of one call (channel groups x work items)
+template <int D, int J>
+hipError_t launch_mf(const KbnSpreadSel &sel, const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
+    const dim3 grid((unsigned)sel.ngr, (unsigned)sel.ny);
+    if constexpr (D == 2) {
         switch (sel.cpt) {
-            case 1: k_spread_os_multi<D, J, 1, 64><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 2: k_spread_os_multi<D, J, 2, 64><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 4: k_spread_os_multi<D, J, 4, 64><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 8: k_spread_os_multi<D, J, 8, 64><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 16: k_spread_os_multi<D, J, 16, 64><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            default: k_spread_os_multi<D, J, 32, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
+            case 8: k_spread_mf2<J, 4, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
+            case 16: k_spread_mf2<J, 2, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
+            case 32: k_spread_mf2<J, 1, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
+            default: k_spread_mf2<J, 1, 2><<<grid, dim3(256), 0, s>>>(g, a); break;
         }
     } else {
+        if (a.M > 0) {
+            const dim3 pgrid((unsigned)((a.M * sel.cpt + KBN_BLOCK - 1) / KBN_BLOCK), (unsigned)sel.ngr);
+            k_permute_groups<<<pgrid, dim3(KBN_BLOCK), 0, s>>>(a.y, a.ys, a.order, a.M, a.nch, sel.cpt);
+        }
         switch (sel.cpt) {
-            case 1: k_spread_os_multi<D, J, 1, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 2: k_spread_os_multi<D, J, 2, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 4: k_spread_os_multi<D, J, 4, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 8: k_spread_os_multi<D, J, 8, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            case 16: k_spread_os_multi<D, J, 16, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
-            default: k_spread_os_multi<D, J, 32, 32><<<grid, blk, sel.lds, s>>>(jobs, ystart, njobs); break;
+            case 8: k_spread_mf3<J, 1, 1><<<grid, dim3(512), 0, s>>>(g, a); break;
+            case 4: k_spread_mf3<J, 2, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
+            case 2: k_spread_mf3<J, 4, 2><<<grid, dim3(256), 0, s>>>(g, a); break;
+            default: k_spread_mf3<J, 8, 4><<<grid, dim3(256), 0, s>>>(g, a); break;
         }
     }
     return hipGetLastError();
@@ -1238,10 +1379,7 @@ hipError_t launch_os_multi(const KbnSpreadSel &sel, dim3 grid, const KbnSpreadJo
 template <int D>
 hipError_t spread_combine(const KbnSpreadSel &sel, const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
     if (a.ncomb_max <= 0) return hipSuccess;
-    if (sel.path == KBN_SPREAD_PATH_CL) {
-        const int ny = std::max(1, std::min(a.ncomb_max, 8 * 256 * 4 / a.nch + 1));
-        k_spread_combine<D><<<dim3((unsigned)a.nch, (unsigned)ny), dim3(64), 0, s>>>(g, a);
-    } else if (sel.path == KBN_SPREAD_PATH_OS) {
+    if (sel.path != KBN_SPREAD_PATH_GENERIC) {
         const int cb = std::min(KBN_BLOCK, (sel.tcells + 63) / 64 * 64);
         const int ny = std::max(1, std::min(a.ncomb_max, 8 * 256 * 4 / a.nch + 1));
         k_spread_combine<D><<<dim3((unsigned)a.nch, (unsigned)ny), dim3(cb), 0, s>>>(g, a);
@@ -1256,12 +1394,10 @@ hipError_t spread_dj(const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
     if (a.nch == 0) return hipSuccess;
     const KbnSpreadSel sel = kbn_spread_select(g, a);
     hipError_t e = hipSuccess;
-    if (sel.path == KBN_SPREAD_PATH_CL) {
-        dim3 grid_cl((unsigned)((a.nch + 63) / 64), (unsigned)std::min(a.nwork_max, KBN_GRID_Y_MAX));
-        k_spread_cl<J, KBN_SPREAD_CL_EB><<<grid_cl, dim3(64), 0, s>>>(g, a);
-        e = hipGetLastError();
+    if (sel.path == KBN_SPREAD_PATH_MF) {
+        if constexpr (D >= 2) e = launch_mf<D, J>(sel, g, a, s);
     } else if (sel.path == KBN_SPREAD_PATH_OS) {
-        e = launch_os<D, J>(sel, dim3((unsigned)sel.ngr, (unsigned)sel.ny), g, a, s);
+        if constexpr (D == 2) e = launch_os<J>(sel, dim3((unsigned)sel.ngr, (unsigned)sel.ny), g, a, s);
     } else {
         const SpreadShape sh = spread_shape(g, a.nch);
         const int ngroup = sh.nwave * sh.cw;
@@ -1321,34 +1457,16 @@ hipError_t spread_d(const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
     }
 }
 
-template <int D>
-hipError_t spread_os_multi_d(const KbnSpreadSel &sel, int J, dim3 grid, const KbnSpreadJob *jobs, const int *ystart,
-                             int njobs, hipStream_t s) {
-    switch (J) {
-        case 2: return launch_os_multi<D, 2>(sel, grid, jobs, ystart, njobs, s);
-        case 3: return launch_os_multi<D, 3>(sel, grid, jobs, ystart, njobs, s);
-        case 4: return launch_os_multi<D, 4>(sel, grid, jobs, ystart, njobs, s);
-        case 5: return launch_os_multi<D, 5>(sel, grid, jobs, ystart, njobs, s);
-        case 6: return launch_os_multi<D, 6>(sel, grid, jobs, ystart, njobs, s);
-        case 7: return launch_os_multi<D, 7>(sel, grid, jobs, ystart, njobs, s);
-        default: return launch_os_multi<D, 8>(sel, grid, jobs, ystart, njobs, s);
-    }
-}
-
 }  // namespace
 
-// Which spread kernel a call takes, with its launch shape: the
-// channel-per-lane kernel (2D 8 x 8 owner tiles, at least 64 channels and
-// enough tiles x channel groups to fill the chip's wave slots twice), the
-// output-stationary one (2D/3D owner tiles of at most 512 cells), else the
-// scatter kernel.  All give the same sums for finite data.
+// Which spread kernel a call takes, with its launch shape: the matrix-core
+// kernels (2D/3D owner tiles of at most 8 cells per axis: every plan with the
+// default owner tile, except J = 8 with a grid edge of 18, 20, 25 or 27, which
+// no split into 7- and 8-cell tiles fits), the output-stationary one (2D owner tiles of at
+// most 512 cells), else the scatter kernel.
 KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a) {
     static const bool os_on = [] {
         const char *e = std::getenv("KBN_SPREAD_OS");
-        return !(e && e[0] == '0');
-    }();
-    static const bool cl_on = [] {
-        const char *e = std::getenv("KBN_SPREAD_CL");
         return !(e && e[0] == '0');
     }();
     KbnSpreadSel sel;
@@ -1359,13 +1477,19 @@ KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a) {
         tmax = std::max(tmax, g.To[d]);
     }
     sel.tcells = tcells;
-    const int64_t cl_waves = (int64_t)g.ntiles_own * ((a.nch + 63) / 64);
-    if (D == 2 && os_on && cl_on && g.To[0] == 8 && g.To[1] == 8 && a.nch >= 64 && cl_waves >= 4096 &&
-        64 * a.M * (int64_t)sizeof(float2) < ((int64_t)1 << 31)) {
-        sel.path = KBN_SPREAD_PATH_CL;
+    if (D >= 2 && tmax <= 8 && os_on) {
+        sel.path = KBN_SPREAD_PATH_MF;
+        // channels per workgroup: 2D 8 to 64; 3D the 8 channels of a matrix
+        // operand, or fewer with more slices in it
+        if (D == 2)
+            sel.cpt = a.nch <= 8 ? 8 : (a.nch <= 16 ? 16 : (a.nch <= 32 ? 32 : 64));
+        else
+            sel.cpt = a.nch <= 1 ? 1 : (a.nch <= 2 ? 2 : (a.nch <= 4 ? 4 : 8));
+        sel.ngr = (a.nch + sel.cpt - 1) / sel.cpt;
+        sel.ny = std::min(a.nwork_max, KBN_GRID_Y_MAX);
         return sel;
     }
-    if (D >= 2 && tcells <= 512 && os_on) {
+    if (D == 2 && tcells <= 512 && os_on) {
         sel.path = KBN_SPREAD_PATH_OS;
         const int want = std::min(a.nch, 32);
         int cpt = 1;
@@ -1373,9 +1497,6 @@ KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a) {
         sel.cpt = cpt;
         sel.ngr = (a.nch + cpt - 1) / cpt;
         sel.ny = std::min(a.nwork_max, KBN_GRID_Y_MAX);
-        // entries per batch of the chosen kernel, and the 3D weight tables
-        sel.ebv = D == 3 ? (cpt <= 16 ? 64 : 32) : 32;
-        sel.lds = D == 3 ? sizeof(float) * (size_t)sel.ebv * D * tmax : 0;
         return sel;
     }
     sel.path = KBN_SPREAD_PATH_GENERIC;
@@ -1413,12 +1534,19 @@ hipError_t kbn_launch_spread(const KbnGeom &g, const KbnSpreadArgs &a, hipStream
     }
 }
 
-hipError_t kbn_launch_spread_os_multi(const KbnSpreadSel &sel, int D, int J, int maxngr, const KbnSpreadJob *jobs,
+hipError_t kbn_launch_spread_os_multi(const KbnSpreadSel &sel, int J, int maxngr, const KbnSpreadJob *jobs,
                                       const int *ystart, int njobs, int total_y, hipStream_t s) {
     if (njobs == 0 || total_y == 0) return hipSuccess;
     const dim3 grid((unsigned)maxngr, (unsigned)total_y);
-    if (D == 2) return spread_os_multi_d<2>(sel, J, grid, jobs, ystart, njobs, s);
-    return spread_os_multi_d<3>(sel, J, grid, jobs, ystart, njobs, s);
+    switch (J) {
+        case 2: return launch_os_multi<2>(sel, grid, jobs, ystart, njobs, s);
+        case 3: return launch_os_multi<3>(sel, grid, jobs, ystart, njobs, s);
+        case 4: return launch_os_multi<4>(sel, grid, jobs, ystart, njobs, s);
+        case 5: return launch_os_multi<5>(sel, grid, jobs, ystart, njobs, s);
+        case 6: return launch_os_multi<6>(sel, grid, jobs, ystart, njobs, s);
+        case 7: return launch_os_multi<7>(sel, grid, jobs, ystart, njobs, s);
+        default: return launch_os_multi<8>(sel, grid, jobs, ystart, njobs, s);
+    }
 }
 
 hipError_t kbn_launch_spread_combine(const KbnSpreadSel &sel, const KbnGeom &g, const KbnSpreadArgs &a,

@@ -14,6 +14,7 @@
 #define KBN_MAX_STAGES 24
 #define KBN_MAX_K 1024      // largest oversampled grid edge handled by the LDS FFT
 #define KBN_MAX_TILES 40959 // tile histograms live in LDS (ntiles + 1 counters, at most 160 KiB)
+#define KBN_MAX_OWN (1 << 21) // spread owner tiles (their counters live in global memory)
 #define KBN_BLOCK 256
 #define KBN_INDEX_STREAM_MIN 8192  // points from which the index pass runs beside the caller's stream
 #define KBN_SUB 256        // sorted points per gather subproblem (one per thread)
@@ -21,17 +22,8 @@
 #define KBN_SPREAD_EB 64   // list entries staged per spread batch
 #define KBN_SPREAD_SEG 128  // list entries per spread work item (doubled if slots run out)
 #define KBN_SPREAD_SMAX 256 // partial-tile slots for tiles split into several work items
-#define KBN_GRID_Y_MAX 65535 // output-stationary spreads stride over work items beyond this many workgroup rows
-#ifndef KBN_SPREAD_CL_WAVES
-#define KBN_SPREAD_CL_WAVES 2 // waves per SIMD the channel-per-lane spread is compiled for
-#endif
-#ifndef KBN_SPREAD_CL_EB
-#define KBN_SPREAD_CL_EB 16 // list entries staged per batch of the channel-per-lane spread
-#endif
+#define KBN_GRID_Y_MAX 65535 // spreads stride over work items beyond this many workgroup rows
 #define KBN_SPREAD_LDS (64 * 1024)  // LDS budget of one spread workgroup
-#ifndef KBN_SPREAD_OS_U
-#define KBN_SPREAD_OS_U 3   // entries per step of the 3D cell-per-lane spread's walk
-#endif
 
 // kernel classes reported by kbn_timing_read (order of kClassNames)
 #define KBN_CLASS_INDEX 0
@@ -59,11 +51,29 @@ struct KbnGeom {
     int T[KBN_MAX_D];
     int nt[KBN_MAX_D];
     int ntiles;
-    int To[KBN_MAX_D];  // spread owner tile edge per axis
+    int To[KBN_MAX_D];  // largest spread owner tile edge per axis (own_lo)
     int nto[KBN_MAX_D];
     int ntiles_own;
     const float *coef;  // [J][KBN_NCOEF] monomial coefficients in x = 2 f - 1
 };
+
+// Spread owner tiles: the n tiles of an axis of K cells split it evenly, tile
+// t holding cells [own_lo(t), own_lo(t + 1)), so that edges differ by at most
+// one (a fixed edge would leave a short last tile, which a J-tap footprint
+// can span: with 8-cell tiles K = 180 would need 9-cell ones instead).
+__host__ __device__ inline int own_lo(int t, int K, int n) { return t * K / n; }
+__host__ __device__ inline int own_tile(int cell, int K, int n) { return ((cell + 1) * n - 1) / K; }
+
+// workgroups of a kernel that can be resident on the current device at once
+template <class K>
+inline int64_t kbn_resident_blocks(K kernel, int nt, size_t lds) {
+    int nb = 0, dev = 0, cus = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kernel, nt, lds) != hipSuccess || nb < 1) nb = 1;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 1;
+    return (int64_t)nb * cus;
+}
 
 // ---------------------------------------------------------------------------
 // Index pass (points.hip)
@@ -105,7 +115,7 @@ hipError_t kbn_launch_points(int D, int64_t M, const float *omega, const double 
 hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, const float *frac,
                                   const int *toff, const int *order, int *ocount, int *ooff,
                                   int *otile_order, int seg, int smax, int *swork, int *scomb, int *scounts,
-                                  int *rec_p, int *rec_q, int *rec_l, float *rec_f, hipStream_t s);
+                                  int *rec_p, int *rec_q, int2 *rec_t, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // FFT passes (fft.hip)
@@ -236,8 +246,7 @@ struct KbnSpreadArgs {
     float2 *partial;           // [smax][nch][prod To] partial tiles of multi-item tiles
     const int *rec_p;          // per owner-list entry: sorted sample position
     const int *rec_q;          // per owner-list entry: the sample's index in the caller's order
-    const int *rec_l;          // [entries][D] tap origin relative to the owning tile
-    const float *rec_f;        // [entries][D] window fraction
+    const int2 *rec_t;         // [entries][D] tap origin relative to the owning tile, window fraction (float bits)
     int nwork_max, ncomb_max;
 };
 
@@ -263,12 +272,12 @@ hipError_t kbn_launch_gather_reduce(const KbnGeom &g, const KbnGatherArgs &a, hi
 
 #define KBN_SPREAD_PATH_GENERIC 0
 #define KBN_SPREAD_PATH_OS 1
-#define KBN_SPREAD_PATH_CL 2
+#define KBN_SPREAD_PATH_MF 2
 struct KbnSpreadSel {
     int path = KBN_SPREAD_PATH_GENERIC;
-    int cpt = 0, ebv = 0, tcells = 0;  // output-stationary: channels per thread, entries per batch, cells
-    size_t lds = 0;                    // its dynamic LDS
-    int ngr = 0, ny = 0;               // its grid: channel groups x work-item rows
+    int cpt = 0;             // channels per thread (output-stationary) or per workgroup (matrix-core)
+    int tcells = 0;          // cells of an owner tile
+    int ngr = 0, ny = 0;     // grid: channel groups x work-item rows
 };
 KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a);
 struct KbnSpreadJob {
@@ -277,11 +286,11 @@ struct KbnSpreadJob {
     int ngr;  // channel groups
     int ny;   // workgroup rows striding over the work items
 };
-// output-stationary spreads of jobs whose kbn_spread_select agree on D, J,
-// cpt, ebv and the owner tile (so one workgroup size); ystart[i] = first
-// row of job i, grid maxngr x total_y.  Each job's split tiles are then
-// summed by kbn_launch_spread_combine.
-hipError_t kbn_launch_spread_os_multi(const KbnSpreadSel &sel, int D, int J, int maxngr, const KbnSpreadJob *jobs,
+// output-stationary spreads (2D) of jobs whose kbn_spread_select agree on J,
+// cpt and the owner tile (so one workgroup size); ystart[i] = first row of
+// job i, grid maxngr x total_y.  Each job's split tiles are then summed by
+// kbn_launch_spread_combine.
+hipError_t kbn_launch_spread_os_multi(const KbnSpreadSel &sel, int J, int maxngr, const KbnSpreadJob *jobs,
                                       const int *ystart, int njobs, int total_y, hipStream_t s);
 hipError_t kbn_launch_spread_combine(const KbnSpreadSel &sel, const KbnGeom &g, const KbnSpreadArgs &a,
                                      hipStream_t s);

@@ -1,4 +1,5 @@
-// Kaiser-Bessel window taps shared by the interpolation kernels (device code).
+// Kaiser-Bessel window taps and the LDS barrier shared by the interpolation
+// and index kernels (device code).
 //
 // Taps: with u = omega K / (2 pi), k_start = floor(u - J/2) + 1 and taps
 // k_start + j, j < J, at distances t_j = u - k_start - j in [-J/2, J/2);
@@ -34,6 +35,15 @@ __device__ __forceinline__ void kb_weights(float f, const float *__restrict__ co
         for (int k = KBN_NCOEF - 2; k >= 0; --k) acc = fmaf(acc, x, coef[j * KBN_NCOEF + k]);
         w[j] = acc;
     }
+}
+
+// Workgroup barrier that orders LDS only: unlike __syncthreads it does not
+// wait for the caller's outstanding global stores.  Where threads exchange
+// data through global memory, __syncthreads is used.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ int wrapk(int i, int K) {  // i in [-K, 2K)

@@ -225,8 +225,8 @@ struct kbn_plan_s {
     int *subs = nullptr, *nsub = nullptr;
     int *ooff = nullptr, *otile_order = nullptr;
     int *swork = nullptr, *scomb = nullptr, *scounts = nullptr;
-    int *rec_p = nullptr, *rec_q = nullptr, *rec_l = nullptr;
-    float *rec_f = nullptr;
+    int *rec_p = nullptr, *rec_q = nullptr;
+    int2 *rec_t = nullptr;
     int64_t swork_cap = 0;
     // grid workspace
     float2 *ws = nullptr;
@@ -353,8 +353,7 @@ void free_points(kbn_plan p, hipStream_t s) {
     dev_free(p, p->swork, s);
     dev_free(p, p->rec_p, s);
     dev_free(p, p->rec_q, s);
-    dev_free(p, p->rec_l, s);
-    dev_free(p, p->rec_f, s);
+    dev_free(p, p->rec_t, s);
     p->swork_cap = 0;
     p->Mcap = 0;
     p->counts_cap = 0;
@@ -491,12 +490,19 @@ int64_t ws_fwd_jac(const kbn_plan p, int64_t M, int B, int C) {
     return units * fwd_jac_per_coil(p) + jac_part_bytes(p, M, units);
 }
 
+// Partial-tile slots for M samples: at most p->smax, and no more than the
+// M 2^D list entries can fill (a split tile of c > SEG entries takes
+// ceil(c / SEG) < 2 c / SEG slots).
+int spread_slots(const kbn_plan p, int64_t M) {
+    return (int)std::min<int64_t>(p->smax, 2 * (M << p->D) / KBN_SPREAD_SEG + 1);
+}
+
 // Type 1 (adjoint): per image-coil pair two grids, the k-space in tile order
 // and the partial tiles of split owner tiles.
 int64_t type1_per_coil(const kbn_plan p, int64_t M) {
     int64_t tcells = 1;
     for (int d = 0; d < p->D; ++d) tcells *= p->To[d];
-    return (p->gsize() * 2 + M + (int64_t)p->smax * tcells) * (int64_t)sizeof(float2);
+    return (p->gsize() * 2 + M + (int64_t)spread_slots(p, M) * tcells) * (int64_t)sizeof(float2);
 }
 
 int64_t ws_type1(const kbn_plan p, int64_t M, int B, int C) {
@@ -518,7 +524,7 @@ PointSizes point_sizes(const kbn_plan p, int64_t M) {
     z.counts = kbn_points_counts_size(M, p->ntiles, p->ntiles_own);
     z.subs = 2 * ((z.cap + KBN_SUB - 1) / KBN_SUB + p->ntiles + 1);
     z.ent = z.cap << p->D;
-    z.swork = p->ntiles_own + (z.ent + KBN_SPREAD_SEG - 1) / KBN_SPREAD_SEG + 1;
+    z.swork = (int64_t)p->ntiles_own + spread_slots(p, M);  // one item per tile, or its share of at most smax slots
     return z;
 }
 
@@ -527,7 +533,7 @@ int64_t points_bytes(const kbn_plan p, int64_t M) {
     const int D = p->D;
     return 4 * block_bytes(4 * z.cap * D) + 2 * block_bytes(4 * z.cap) + block_bytes(4 * z.counts) +
            block_bytes(4 * z.subs) + block_bytes(16 * z.swork) + 2 * block_bytes(4 * z.ent) +
-           2 * block_bytes(4 * z.ent * D);
+           block_bytes(8 * z.ent * D);
 }
 
 // FFT passes of one forward-type chunk (nb images from b0, ncc coils from
@@ -674,10 +680,9 @@ KbnSpreadArgs t1_spread_args(kbn_plan p, int64_t nch, const float2 *y_chunk, flo
     sa.partial = bufP;
     sa.rec_p = p->rec_p;
     sa.rec_q = p->rec_q;
-    sa.rec_l = p->rec_l;
-    sa.rec_f = p->rec_f;
+    sa.rec_t = p->rec_t;
     sa.nwork_max = (int)p->swork_cap;
-    sa.ncomb_max = std::min<int>(p->ntiles_own, p->smax / 2);
+    sa.ncomb_max = std::min<int>(p->ntiles_own, spread_slots(p, p->M) / 2);
     return sa;
 }
 
@@ -1117,23 +1122,24 @@ int plan_setup(kbn_plan p, int D, const int64_t *N, const kbn_opts *opts) {
     }
     if (ntiles > KBN_MAX_TILES) return fail(KBN_ERR_UNSUPPORTED, "too many tiles; use larger tiles");
     p->ntiles = (int)ntiles;
-    // spread owner tiles: small enough that several channels' accumulators fit
-    // in LDS, large enough that the tile count fits the LDS histogram
+    // spread owner tiles: even splits of each axis near the preferred edge, at
+    // least J - 1 wide so that a J-tap footprint meets at most two per axis
     int64_t ntiles_own = 1;
     int defown = o.spread_tile > 0 ? std::max(J, o.spread_tile) : (D == 1 ? 128 : 8);
     for (;;) {
         ntiles_own = 1;
         for (int d = 0; d < D; ++d) {
             const int K = p->K[d];
-            const int T = pick_tile(K, defown, J);
-            p->To[d] = T;
-            p->nto[d] = (K + T - 1) / T;
-            ntiles_own *= p->nto[d];
+            int n = std::max(1, (K + defown - 1) / defown);
+            while (n > 1 && K / n < J - 1) --n;
+            p->To[d] = (K + n - 1) / n;
+            p->nto[d] = n;
+            ntiles_own *= n;
         }
-        if (ntiles_own <= KBN_MAX_TILES || defown >= KBN_MAX_K) break;
+        if (ntiles_own <= KBN_MAX_OWN || defown >= KBN_MAX_K) break;
         defown += 4;
     }
-    if (ntiles_own > KBN_MAX_TILES) {
+    if (ntiles_own > KBN_MAX_OWN) {
         return fail(KBN_ERR_UNSUPPORTED, "too many spread tiles");
     }
     p->ntiles_own = (int)ntiles_own;
@@ -1188,8 +1194,8 @@ int index_pass(kbn_plan p, int64_t M, const float *omega, const KbnPointsBufs &b
     KBN_LAUNCH(KBN_CLASS_INDEX,
                kbn_launch_owner_lists(p->geom(), M, p->cell, p->frac, p->toff, p->order,
                                       p->counts + kbn_points_owner_base(M, p->ntiles), p->ooff, p->otile_order,
-                                      KBN_SPREAD_SEG, p->smax, p->swork, p->scomb, p->scounts, p->rec_p, p->rec_q,
-                                      p->rec_l, p->rec_f, stream),
+                                      KBN_SPREAD_SEG, spread_slots(p, M), p->swork, p->scomb, p->scounts, p->rec_p, p->rec_q,
+                                      p->rec_t, stream),
                "spread lists");
     return KBN_OK;
 }
@@ -1305,8 +1311,7 @@ int kbn_set_points(kbn_plan p, int64_t M, const float *omega, void *stream_) {
         if (rc == KBN_OK) rc = dev_alloc(p, &p->swork, 4 * z.swork, stream);
         if (rc == KBN_OK) rc = dev_alloc(p, &p->rec_p, z.ent, stream);
         if (rc == KBN_OK) rc = dev_alloc(p, &p->rec_q, z.ent, stream);
-        if (rc == KBN_OK) rc = dev_alloc(p, &p->rec_l, z.ent * D, stream);
-        if (rc == KBN_OK) rc = dev_alloc(p, &p->rec_f, z.ent * D, stream);
+        if (rc == KBN_OK) rc = dev_alloc(p, &p->rec_t, z.ent * D, stream);
         if (rc != KBN_OK) {
             const std::string msg = g_err;
             free_points(p, stream);

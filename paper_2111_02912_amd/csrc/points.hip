@@ -79,15 +79,6 @@ k_points_hist(int D, int64_t M, int chunk, int nchunks, int nbins, const float *
     for (int i = threadIdx.x; i < nbins; i += blockDim.x) counts[(int64_t)i * nchunks + ch] = hist[i];
 }
 
-// Workgroup barrier that orders LDS only: unlike __syncthreads it does not
-// wait for the caller's outstanding global stores.  Where threads exchange
-// data through global memory, __syncthreads is used.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ __forceinline__ int block_scan_1024(int x, int *wsum, int &total) {
     // inclusive scan over a 1024-thread block; returns the exclusive prefix
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
@@ -327,7 +318,7 @@ k_tile_scatter(int64_t M, int chunk, int nchunks, int nbins, int nbits,
 struct OwnerGeom {
     int D, J, LO, HI;
     int ntiles_sort, ntiles_own;
-    int K[3], To[3], nto[3], T[3], nt[3];
+    int K[3], nto[3], T[3], nt[3];
 };
 
 #define KBN_OWN_BLOCK 256
@@ -345,8 +336,8 @@ __device__ __forceinline__ void owner_span(const OwnerGeom &o, int t, int lo[3],
     for (int d = D - 1; d >= 0; --d) {
         const int a = rem % o.nto[d];
         rem /= o.nto[d];
-        lo[d] = a * o.To[d];
-        hi[d] = min(lo[d] + o.To[d], o.K[d]) - 1;
+        lo[d] = own_lo(a, o.K[d], o.nto[d]);
+        hi[d] = own_lo(a + 1, o.K[d], o.nto[d]) - 1;
     }
 #pragma unroll
     for (int d = 0; d < D; ++d) {
@@ -513,8 +504,8 @@ __device__ __forceinline__ void owner_walk(const OwnerGeom &o, int t, int64_t M,
 // Entry count of every owner tile, pushed from the samples: a finite sample
 // reaches, per axis, the owner tile holding its first tap and, when its J
 // taps cross into the next tile (modulo K), that one too (owner tiles are at
-// least J wide, so these are exactly the tiles whose cells its taps meet, the
-// relation k_owner_write tests).  Lanes of a wavefront that reach the same
+// least J - 1 wide, so these are exactly the tiles whose cells its taps meet,
+// the relation k_owner_write tests).  Lanes of a wavefront that reach the same
 // tile add with one atomic; integer counts do not depend on the order.
 template <int D>
 __global__ void __launch_bounds__(KBN_BLOCK)
@@ -534,8 +525,8 @@ k_owner_count(OwnerGeom o, int64_t M, const int *__restrict__ cell, const float 
             const int sw = st < 0 ? st + K : st;
             int se = sw + o.J - 1;
             if (se >= K) se -= K;
-            first[d] = sw / o.To[d];
-            second[d] = se / o.To[d];
+            first[d] = own_tile(sw, K, o.nto[d]);
+            second[d] = own_tile(se, K, o.nto[d]);
             num[d] = first[d] == second[d] ? 1 : 2;
         }
     }
@@ -568,7 +559,7 @@ __global__ void __launch_bounds__(KBN_OWN_BLOCK)
 k_owner_write(OwnerGeom o, int64_t M, const int *__restrict__ cell, const float *__restrict__ frac,
               const int *__restrict__ toff, const int *__restrict__ order, const int *__restrict__ ooff,
               const int *__restrict__ otile_order, int *__restrict__ rec_p, int *__restrict__ rec_q,
-              int *__restrict__ rec_l, float *__restrict__ rec_f) {
+              int2 *__restrict__ rec_t) {
     __shared__ int cbeg[KBN_OWN_MAXC], coff[KBN_OWN_MAXC + 1];
     __shared__ int wsum[KBN_OWN_BLOCK / 64];
     const int t = otile_order[blockIdx.x];  // tiles with the most entries first
@@ -586,10 +577,8 @@ k_owner_write(OwnerGeom o, int64_t M, const int *__restrict__ cell, const float 
                           rec_p[e] = p[u];
                           rec_q[e] = order[p[u]];
 #pragma unroll
-                          for (int d = 0; d < D; ++d) {
-                              rec_l[(int64_t)e * D + d] = rel[u][d];
-                              rec_f[(int64_t)e * D + d] = fr[u][d];
-                          }
+                          for (int d = 0; d < D; ++d)
+                              rec_t[(int64_t)e * D + d] = make_int2(rel[u][d], __float_as_int(fr[u][d]));
                           ++e;
                       }
                       run += total;
@@ -882,7 +871,7 @@ hipError_t kbn_launch_points(int D, int64_t M, const float *omega, const double 
 hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, const float *frac,
                                   const int *toff, const int *order, int *ocount, int *ooff,
                                   int *otile_order, int seg, int smax, int *swork, int *scomb, int *scounts,
-                                  int *rec_p, int *rec_q, int *rec_l, float *rec_f, hipStream_t s) {
+                                  int *rec_p, int *rec_q, int2 *rec_t, hipStream_t s) {
     OwnerGeom o;
     o.D = g.D;
     o.J = g.J;
@@ -892,7 +881,6 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
     o.ntiles_own = g.ntiles_own;
     for (int d = 0; d < 3; ++d) {
         o.K[d] = d < g.D ? g.K[d] : 1;
-        o.To[d] = d < g.D ? g.To[d] : 1;
         o.nto[d] = d < g.D ? g.nto[d] : 1;
         o.T[d] = d < g.D ? g.T[d] : 1;
         o.nt[d] = d < g.D ? g.nt[d] : 1;
@@ -915,8 +903,7 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
             k_owner_finish<false><<<dim3(1), dim3(1024), 0, s>>>(n, seg, smax, ocount, ooff,           \
                                                                  otile_order, swork, scomb, scounts);  \
         k_owner_write<d><<<dim3(n), dim3(KBN_OWN_BLOCK), 0, s>>>(o, M, cell, frac, toff, order, ooff,  \
-                                                                 otile_order, rec_p, rec_q, rec_l,     \
-                                                                 rec_f);                               \
+                                                                 otile_order, rec_p, rec_q, rec_t);    \
         break;
         KBN_OWN(1) KBN_OWN(2) KBN_OWN(3)
 #undef KBN_OWN
