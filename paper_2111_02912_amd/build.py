@@ -17,8 +17,8 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libkbnufft.so")
 
-SOURCES = ["plan.cpp", "batch.cpp", "points.hip", "fft.hip", "fft_fast.hip", "interp.hip", "cg.hip",
-           "field.hip"]
+SOURCES = ["fft_fast.hip", "interp.hip"] + [f"fft_any_{u}.hip" for u in range(6)] + \
+    ["plan.cpp", "batch.cpp", "points.hip", "fft.hip", "cg.hip", "field.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -470,3 +470,17 @@ hipError_t kbn_launch_last_adj(const KbnLastAdjArgs &a, const KbnRadix &rp, cons
         k_last_adj<16><<<dim3((unsigned)blocks), dim3(KBN_BLOCK), lds, s>>>(a, rp, tw, nl);
     return hipGetLastError();
 }
+
+#define KBN_ANY_DECL(u) KbnAnyPasses kbn_any_passes_##u(int L);
+KBN_ANY_DECL(0) KBN_ANY_DECL(1) KBN_ANY_DECL(2) KBN_ANY_DECL(3) KBN_ANY_DECL(4) KBN_ANY_DECL(5)
+#undef KBN_ANY_DECL
+
+KbnAnyPasses kbn_any_passes(int L) {
+    KbnAnyPasses (*const units[])(int) = {kbn_any_passes_0, kbn_any_passes_1, kbn_any_passes_2,
+                                          kbn_any_passes_3, kbn_any_passes_4, kbn_any_passes_5};
+    for (auto unit : units) {
+        const KbnAnyPasses p = unit(L);
+        if (p.first) return p;
+    }
+    return KbnAnyPasses{};
+}

@@ -1,11 +1,14 @@
-// Compile-time specialised FFT passes for the common oversampled grid sizes.
+// Register-resident FFT passes of the grid lengths 128, 256 and 512, and the
+// column passes of 192, 320 and 640, the ones that measured faster than the
+// passes of fft_any.h (72 images of 320^2: 640-point columns 84 forward and 112
+// inverse against 93 and 122 us; 800 of 96^2: 192-point 74 and 87 against 79 and
+// 92; 256 of 160^2: 320-point 63 and 80 against 67 and 88).
 //
-// Same operations as the generic passes in fft.hip (forward first pass with
-// the scaling / coil / coordinate-weight prologue, strided forward and
+// Same operations as the runtime-length passes in fft.hip (forward first pass
+// with the scaling / coil / coordinate-weight prologue, strided forward and
 // inverse passes with zero-padding and cropping, last inverse pass with
-// crop, scaling and coil sum), for L in a fixed set.  With L and the number
-// E of elements per thread known at compile time, every radix, stride and
-// index is a constant.  Each thread holds the inputs of its E / R
+// crop, scaling and coil sum).  With L and the number E of elements per thread
+// known at compile time, every radix, stride and index is a constant.  Each thread holds the inputs of its E / R
 // butterflies in registers; stage 0 reads them straight from global memory
 // (zero-padding rows are never read), the last stage writes straight to
 // global memory (cropped rows are never written), and only the stages in
@@ -132,19 +135,8 @@ struct SDftOdd {
         }
     }
 };
-template <>
-struct STrig<7> {
-    static constexpr float c[7] = {1.0f, 0.62348980185873353f, -0.22252093395631440f,
-                                   -0.90096886790241912f, -0.90096886790241912f, -0.22252093395631440f,
-                                   0.62348980185873353f};
-    static constexpr float s[7] = {0.0f, 0.78183148246802981f, 0.97492791218182361f,
-                                   0.43388373911755812f, -0.43388373911755812f, -0.97492791218182361f,
-                                   -0.78183148246802981f};
-};
 template <bool INV>
 struct SDft<3, INV> : SDftOdd<3, INV> {};
-template <bool INV>
-struct SDft<7, INV> : SDftOdd<7, INV> {};
 template <bool INV>
 struct SDft<5, INV> : SDftOdd<5, INV> {};
 
@@ -155,7 +147,6 @@ constexpr int pick_radix(int rem, int E) {
            : (rem % 2 == 0 && E % 2 == 0) ? 2
            : (rem % 3 == 0 && E % 3 == 0) ? 3
            : (rem % 5 == 0 && E % 5 == 0) ? 5
-           : (rem % 7 == 0 && E % 7 == 0) ? 7
                                           : 0;
 }
 constexpr int rem_at(int L, int E, int s) {
@@ -554,10 +545,10 @@ __global__ void __launch_bounds__(NT) k_rows_first(KbnFirstPassArgs a, const flo
     Stages<F, 0>::run(v, u, twl, ldsl, lds_idx, sink);
 }
 
-// ---- last inverse pass along the last axis (crop, scaling, coil sum) -------
-// ONE: a single coil (C = 1, with or without a map): each value is weighted
-// and stored as the last stage produces it, with no coil accumulators.
-template <int L, int E, int NT, bool ONE>
+// ---- last inverse pass along the last axis (crop, scaling, coil map) -------
+// One coil a line (C = 1, with or without a map): each value is weighted and
+// stored as the last stage produces it.
+template <int L, int E, int NT>
 __global__ void __launch_bounds__(NT) k_rows_last_adj(KbnLastAdjArgs a, const float2 *__restrict__ tw) {
     using F = Fft<L, E, true>;
     static_assert(NT % F::TL == 0, "a workgroup holds whole lines");
@@ -586,131 +577,44 @@ __global__ void __launch_bounds__(NT) k_rows_last_adj(KbnLastAdjArgs a, const fl
         lf = f;
     }
     const float *deap_l = a.deap[a.D - 1];
-    if constexpr (ONE) {
-        const float2 *in = a.in + line * (int64_t)L;
-        float2 v[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-            const int p = F::template in_pos<0>(u, i);
-            v[i] = line_ok ? in[p] : make_float2(0.f, 0.f);
-        }
-        __syncthreads();  // twiddles in LDS
-        const int cm = a.cmod > 0 ? (int)(bl % a.cmod) : 0;
-        const float2 *srow = a.smaps ? a.smaps + ((int64_t)cm * a.R0 + row) * Nl : nullptr;
-        float2 *x = a.x + line * Nl;
-        auto lds_idx = [](int pos) { return pos; };
-        float2 *ldsl = lds + li * L;
-        auto sink = [&](int, int pos, float2 val) {
-            const int j = pos_to_img<L>(pos, Nl);
-            if (line_ok && j >= 0) {
-                if (srow) val = cmulc(val, srow[j]);
-                const float f = lf * deap_l[j];
-                val = make_float2(val.x * f, val.y * f);
-                if (a.accumulate) {
-                    const float2 o = x[j];
-                    val = make_float2(o.x + val.x, o.y + val.y);
-                }
-                x[j] = val;
-            }
-        };
-        Stages<F, 0>::run(v, u, twl, ldsl, lds_idx, sink);
-        return;
-    }
-    float2 acc[E];
-#pragma unroll
-    for (int i = 0; i < E; ++i) acc[i] = make_float2(0.f, 0.f);
-    __syncthreads();  // twiddles in LDS
-    for (int c = 0; c < a.C; ++c) {
-        const float2 *in = a.in + (((bl * a.C + c) * a.R0) + row) * (int64_t)L;
-        float2 v[E];
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-            const int p = F::template in_pos<0>(u, i);
-            v[i] = line_ok ? in[p] : make_float2(0.f, 0.f);
-        }
-        if (c > 0) __syncthreads();  // previous coil's last LDS reads are done
-        const int cm = a.cmod > 0 ? (int)(bl % a.cmod) : c;
-        const float2 *srow = a.smaps ? a.smaps + ((int64_t)cm * a.R0 + row) * Nl : nullptr;
-        auto lds_idx = [](int pos) { return pos; };
-        float2 *ldsl = lds + li * L;
-        auto sink = [&](int i, int pos, float2 val) {
-            const int j = pos_to_img<L>(pos, Nl);
-            if (line_ok && j >= 0) {
-                if (srow) val = cmulc(val, srow[j]);
-                const float f = lf * deap_l[j];
-                acc[i].x += val.x * f;
-                acc[i].y += val.y * f;
-            }
-        };
-        Stages<F, 0>::run(v, u, twl, ldsl, lds_idx, sink);
-    }
-    // write: register element i of the last stage holds line position out_pos
-    float2 *x = a.x + line * Nl;
+    const float2 *in = a.in + line * (int64_t)L;
+    float2 v[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-        const int pos = F::template out_pos<F::NST - 1>(u, i);
+        const int p = F::template in_pos<0>(u, i);
+        v[i] = line_ok ? in[p] : make_float2(0.f, 0.f);
+    }
+    __syncthreads();  // twiddles in LDS
+    const int cm = a.cmod > 0 ? (int)(bl % a.cmod) : 0;
+    const float2 *srow = a.smaps ? a.smaps + ((int64_t)cm * a.R0 + row) * Nl : nullptr;
+    float2 *x = a.x + line * Nl;
+    auto lds_idx = [](int pos) { return pos; };
+    float2 *ldsl = lds + li * L;
+    auto sink = [&](int, int pos, float2 val) {
         const int j = pos_to_img<L>(pos, Nl);
         if (line_ok && j >= 0) {
+            if (srow) val = cmulc(val, srow[j]);
+            const float f = lf * deap_l[j];
+            val = make_float2(val.x * f, val.y * f);
             if (a.accumulate) {
                 const float2 o = x[j];
-                x[j] = make_float2(o.x + acc[i].x, o.y + acc[i].y);
-            } else {
-                x[j] = acc[i];
+                val = make_float2(o.x + val.x, o.y + val.y);
             }
+            x[j] = val;
         }
-    }
+    };
+    Stages<F, 0>::run(v, u, twl, ldsl, lds_idx, sink);
 }
 
-// Elements per thread for each specialised length: rows (last axis) and
-// columns (strided axes, at most 64 KiB of LDS per workgroup).  Every radix
-// of a length's plan must divide E (radices 8, 4, 2, 3, 5), L / E threads
-// serve one line and a workgroup holds whole lines: 400 = 2^4 5^2 takes
-// E = 20 (radices 4,4,5,5) with 20 threads per line in 320-thread
-// workgroups; 480 = 2^5 3 5 takes E = 60 (4,4,2,3,5) with 128 threads.
-// Per-length configuration: elements per thread of the row and column
-// passes (every radix of the length's plan must divide them, so lengths with
-// factors 2, 3 and 5 take 30 and those with 2, 3 and 7 take 42) and, for
-// lengths whose line does not divide 256 threads, the lines (row passes) or
-// columns (column passes) a workgroup holds, within 64 KB of LDS (80 KB for
-// the 16 columns of 640, which read whole 128-byte row segments: 28% faster
-// than 8 columns, while 768 with 16 columns, 96 KB, fits one workgroup per
-// CU and loses); 0 keeps the tuned thread counts of row_nt / col_nt.  Row passes are LDS-occupancy
-// bound, so they take the smaller E where a length allows two.
-struct FftLen {
-    int L, re, ce, rl, cl;
-};
-constexpr FftLen kFftLens[] = {
-    {128, 8, 8, 0, 0},     {160, 10, 20, 0, 0},   {192, 12, 12, 0, 0},   {200, 20, 20, 8, 16},
-    {256, 8, 16, 0, 0},    {270, 30, 30, 16, 16}, {288, 12, 24, 8, 16},  {300, 30, 30, 16, 16},
-    {320, 10, 20, 0, 0},   {324, 12, 12, 8, 8},   {360, 30, 30, 16, 16}, {384, 12, 24, 0, 0},
-    {392, 14, 28, 8, 16},
-    {400, 10, 20, 0, 0},   {432, 12, 24, 8, 16},  {448, 28, 28, 8, 16},  {450, 30, 30, 8, 16},
-    {480, 60, 60, 0, 0},   {486, 18, 18, 8, 8},   {500, 20, 20, 8, 8},   {504, 42, 42, 8, 16},
-    {512, 8, 16, 0, 0},    {540, 30, 30, 8, 8},   {576, 12, 24, 8, 8},   {588, 42, 42, 8, 8},
-    {600, 30, 30, 8, 8},   {640, 10, 20, 0, 16},  {648, 24, 24, 8, 8},   {672, 42, 42, 8, 8},
-    {686, 14, 14, 8, 8},   {720, 30, 30, 8, 8},   {750, 30, 30, 8, 8},   {756, 42, 42, 8, 8},
-    {768, 24, 24, 0, 0},   {800, 20, 20, 8, 8},   {1024, 16, 32, 0, 0},
-};
-constexpr FftLen fft_len(int L) {
-    for (const FftLen &f : kFftLens)
-        if (f.L == L) return f;
-    return FftLen{L, 0, 0, 0, 0};
-}
-constexpr int row_e(int L) { return fft_len(L).re; }
-constexpr int col_e(int L) { return fft_len(L).ce; }
-// threads per row-pass workgroup (whole lines of L / E threads each)
-constexpr int row_nt(int L) {
-    return fft_len(L).rl ? fft_len(L).rl * (L / row_e(L)) : L == 400 ? 320 : L == 480 ? 128 : KBN_BLOCK;
-}
-// threads per column-pass workgroup (512 for L = 512: 16 columns of 32
-// threads, 64 KB of LDS, measured faster than 256 threads with E = 32)
-constexpr int col_nt(int L) {
-    return fft_len(L).cl ? fft_len(L).cl * (L / col_e(L))
-           : L == 512    ? 512
-           : L == 400    ? 320
-           : L == 480    ? 128
-                         : KBN_BLOCK;
-}
+// Elements per thread of the row and column passes (every radix of the
+// length's plan must divide them).  Row passes are LDS-occupancy bound, so they
+// take the smaller E.
+constexpr int row_e(int L) { return 8; }
+constexpr int col_e(int L) { return L == 128 ? 8 : L == 192 ? 12 : L % 5 == 0 ? 20 : 16; }
+// threads per column-pass workgroup: 512 for L = 512 and 640 (16 columns, which
+// read whole 128-byte row segments; 512: 64 KB of LDS, measured faster than 256
+// threads with E = 32; 640: 80 KB, 28% faster than 8 columns)
+constexpr int col_nt(int L) { return L == 512 || L == 640 ? 512 : KBN_BLOCK; }
 
 // column passes that load ahead (L = 512: 0.65 -> 0.45 ms forward, 0.22 ->
 // 0.19 ms inverse for 256 images of 512 x 512 on MI355X; 128 and 256: 3-8%);
@@ -787,7 +691,7 @@ hipError_t launch_cols(const KbnMidPassArgs &a, const float2 *tw, int inverse, h
 template <int L>
 hipError_t launch_rows_first(const KbnFirstPassArgs &a, const float2 *tw, hipStream_t s) {
     constexpr int E = row_e(L);
-    constexpr int NT = row_nt(L);
+    constexpr int NT = KBN_BLOCK;
     constexpr int LINES = NT / (L / E);
     const dim3 grid((unsigned)((a.nlines + LINES - 1) / LINES));
     k_rows_first<L, E, NT><<<grid, dim3(NT), 0, s>>>(a, tw);
@@ -797,44 +701,32 @@ hipError_t launch_rows_first(const KbnFirstPassArgs &a, const float2 *tw, hipStr
 template <int L>
 hipError_t launch_rows_last(const KbnLastAdjArgs &a, const float2 *tw, hipStream_t s) {
     constexpr int E = row_e(L);
-    constexpr int NT = row_nt(L);
+    constexpr int NT = KBN_BLOCK;
     constexpr int LINES = NT / (L / E);
     const dim3 grid((unsigned)((a.nlines + LINES - 1) / LINES));
-    if (a.C == 1)
-        k_rows_last_adj<L, E, NT, true><<<grid, dim3(NT), 0, s>>>(a, tw);
-    else
-        k_rows_last_adj<L, E, NT, false><<<grid, dim3(NT), 0, s>>>(a, tw);
+    k_rows_last_adj<L, E, NT><<<grid, dim3(NT), 0, s>>>(a, tw);
     return hipGetLastError();
 }
 
-#define KBN_FAST_SIZES(X) \
-    X(128) X(160) X(192) X(200) X(256) X(270) X(288) X(300) X(320) X(324) X(360) X(384) X(392) X(400) \
-    X(432) X(448) X(450) X(480) X(486) X(500) X(504) X(512) X(540) X(576) X(588) X(600) X(640) X(648) \
-    X(672) X(686) X(720) X(750) X(756) X(768) X(800) X(1024)
-// the last adjoint pass keeps E accumulators besides the E values, which
-// spills for 480 (E = 60), 504, 588, 756 (E = 42) and 800: those lengths
-// take the generic last pass
-#define KBN_FAST_LAST_SIZES(X) \
-    X(128) X(160) X(192) X(200) X(256) X(270) X(288) X(300) X(320) X(324) X(360) X(384) X(392) X(400) \
-    X(432) X(448) X(450) X(486) X(500) X(512) X(540) X(576) X(600) X(640) X(648) X(672) X(686) X(720) \
-    X(750) X(768) X(1024)
+#define KBN_FAST_ROWS(X) X(128) X(256) X(512)
+#define KBN_FAST_COLS(X) X(128) X(192) X(256) X(320) X(512) X(640)
 
 }  // namespace
 
-bool kbn_fast_fft_size(int L) {
+bool kbn_fast_cols_size(int L) {
     switch (L) {
 #define KBN_CASE(n) case n:
-        KBN_FAST_SIZES(KBN_CASE)
+        KBN_FAST_COLS(KBN_CASE)
 #undef KBN_CASE
         return true;
         default: return false;
     }
 }
 
-bool kbn_fast_last_size(int L) {
+bool kbn_fast_rows_size(int L) {
     switch (L) {
 #define KBN_CASE(n) case n:
-        KBN_FAST_LAST_SIZES(KBN_CASE)
+        KBN_FAST_ROWS(KBN_CASE)
 #undef KBN_CASE
         return true;
         default: return false;
@@ -845,7 +737,7 @@ hipError_t kbn_launch_fast_mid(const KbnMidPassArgs &a, int L, const float2 *tw,
                                hipStream_t s) {
     switch (L) {
 #define KBN_CASE(n) case n: return launch_cols<n>(a, tw, inverse, s);
-        KBN_FAST_SIZES(KBN_CASE)
+        KBN_FAST_COLS(KBN_CASE)
 #undef KBN_CASE
         default: return hipErrorInvalidValue;
     }
@@ -854,7 +746,7 @@ hipError_t kbn_launch_fast_mid(const KbnMidPassArgs &a, int L, const float2 *tw,
 hipError_t kbn_launch_fast_first(const KbnFirstPassArgs &a, int L, const float2 *tw, hipStream_t s) {
     switch (L) {
 #define KBN_CASE(n) case n: return launch_rows_first<n>(a, tw, s);
-        KBN_FAST_SIZES(KBN_CASE)
+        KBN_FAST_ROWS(KBN_CASE)
 #undef KBN_CASE
         default: return hipErrorInvalidValue;
     }
@@ -863,7 +755,7 @@ hipError_t kbn_launch_fast_first(const KbnFirstPassArgs &a, int L, const float2 
 hipError_t kbn_launch_fast_last(const KbnLastAdjArgs &a, int L, const float2 *tw, hipStream_t s) {
     switch (L) {
 #define KBN_CASE(n) case n: return launch_rows_last<n>(a, tw, s);
-        KBN_FAST_LAST_SIZES(KBN_CASE)
+        KBN_FAST_ROWS(KBN_CASE)
 #undef KBN_CASE
         default: return hipErrorInvalidValue;
     }

@@ -182,16 +182,23 @@ hipError_t kbn_launch_last_adj(const KbnLastAdjArgs &a, const KbnRadix &rp, cons
                                int maxe, hipStream_t s);
 int kbn_lines_per_block(const KbnRadix &rp, int maxe);
 
-// Compile-time specialised passes (fft_fast.hip) for the lengths where
-// kbn_fast_fft_size() is true; they return hipErrorInvalidValue otherwise.
-bool kbn_fast_fft_size(int L);
-// the specialised last adjoint pass exists for a subset of those lengths (it
-// holds E accumulators besides the E values: above E = 32 it would spill)
-bool kbn_fast_last_size(int L);
+// Register-resident passes (fft_fast.hip) for the lengths where these are true;
+// they return hipErrorInvalidValue otherwise.
+bool kbn_fast_rows_size(int L);
+bool kbn_fast_cols_size(int L);
 hipError_t kbn_launch_fast_first(const KbnFirstPassArgs &a, int L, const float2 *tw, hipStream_t s);
 hipError_t kbn_launch_fast_mid(const KbnMidPassArgs &a, int L, const float2 *tw, int inverse,
                                hipStream_t s);
 hipError_t kbn_launch_fast_last(const KbnLastAdjArgs &a, int L, const float2 *tw, hipStream_t s);
+
+// Compile-time passes of every 7-smooth length but 128, 256 and 512 (fft_any.h,
+// compiled in six groups): null members for those.
+struct KbnAnyPasses {
+    hipError_t (*first)(const KbnFirstPassArgs &a, const float2 *tw, hipStream_t s) = nullptr;
+    hipError_t (*mid)(const KbnMidPassArgs &a, const float2 *tw, int inverse, hipStream_t s) = nullptr;
+    hipError_t (*last)(const KbnLastAdjArgs &a, const float2 *tw, hipStream_t s) = nullptr;
+};
+KbnAnyPasses kbn_any_passes(int L);
 
 // ---------------------------------------------------------------------------
 // Interpolation (interp.hip)

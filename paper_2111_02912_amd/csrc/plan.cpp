@@ -215,7 +215,8 @@ struct kbn_plan_s {
     float *coef = nullptr;
     int *flag = nullptr;
     int maxe = 16;
-    bool fast_fft = true;  // use the specialised FFT passes where available
+    bool fast_fft = true;  // use the compile-time FFT passes
+    KbnAnyPasses any[KBN_MAX_D];  // those of each axis (fft_any.h)
     // points
     int64_t M = -1, Mcap = 0;
     int *cell_tmp = nullptr, *tile = nullptr, *order = nullptr, *cell = nullptr, *toff = nullptr;
@@ -536,6 +537,26 @@ int64_t points_bytes(const kbn_plan p, int64_t M) {
            block_bytes(8 * z.ent * D);
 }
 
+// One FFT pass along axis d (the first and last passes: the last axis): the
+// register-resident form of the few lengths that have one, else the
+// compile-time pass of the length, or (KBN_GENERIC_FFT=1) the runtime-length one.
+hipError_t launch_first(kbn_plan p, const KbnFirstPassArgs &a, hipStream_t s) {
+    const int d = p->D - 1, K = p->K[d];
+    if (!p->fast_fft) return kbn_launch_first_pass(a, p->rad[d], p->tw[d], p->maxe, s);
+    return kbn_fast_rows_size(K) ? kbn_launch_fast_first(a, K, p->tw[d], s) : p->any[d].first(a, p->tw[d], s);
+}
+hipError_t launch_mid(kbn_plan p, int d, const KbnMidPassArgs &a, int inverse, hipStream_t s) {
+    const int K = p->K[d];
+    if (!p->fast_fft) return kbn_launch_mid_pass(a, p->rad[d], p->tw[d], inverse, p->maxe, s);
+    return kbn_fast_cols_size(K) ? kbn_launch_fast_mid(a, K, p->tw[d], inverse, s)
+                                 : p->any[d].mid(a, p->tw[d], inverse, s);
+}
+hipError_t launch_last(kbn_plan p, const KbnLastAdjArgs &a, hipStream_t s) {
+    const int d = p->D - 1, K = p->K[d];
+    if (!p->fast_fft) return kbn_launch_last_adj(a, p->rad[d], p->tw[d], p->maxe, s);
+    return kbn_fast_rows_size(K) ? kbn_launch_fast_last(a, K, p->tw[d], s) : p->any[d].last(a, p->tw[d], s);
+}
+
 // FFT passes of one forward-type chunk (nb images from b0, ncc coils from
 // c0, nw weight channels per coil): scaling (+ coil map, + coordinate
 // weight) and the last-axis pass into bufA, then the strided passes
@@ -562,13 +583,7 @@ int t2_passes(kbn_plan p, int nw, int weighted, const float2 *x, const float2 *s
         fa.N[d] = p->N[d];
         fa.deap[d] = p->deap[d];
     }
-    if (p->fast_fft && kbn_fast_fft_size(p->K[D - 1]))
-        KBN_LAUNCH(KBN_CLASS_FFT_FIRST, kbn_launch_fast_first(fa, p->K[D - 1], p->tw[D - 1], stream),
-                   "first pass");
-    else
-        KBN_LAUNCH(KBN_CLASS_FFT_FIRST,
-                   kbn_launch_first_pass(fa, p->rad[D - 1], p->tw[D - 1], p->maxe, stream),
-                   "first pass");
+    KBN_LAUNCH(KBN_CLASS_FFT_FIRST, launch_first(p, fa, stream), "first pass");
     float2 *cur = bufA, *nxt = bufB;
     for (int d = D - 2; d >= 0; --d) {
         int64_t outer = nch, inner = 1;
@@ -583,12 +598,7 @@ int t2_passes(kbn_plan p, int nw, int weighted, const float2 *x, const float2 *s
         ma.inner = (int)inner;
         ma.pad_in = 1;
         ma.crop_out = 0;
-        if (p->fast_fft && kbn_fast_fft_size(p->K[d]))
-            KBN_LAUNCH(KBN_CLASS_FFT_MID_FWD, kbn_launch_fast_mid(ma, p->K[d], p->tw[d], 0, stream),
-                       "mid pass");
-        else
-            KBN_LAUNCH(KBN_CLASS_FFT_MID_FWD,
-                       kbn_launch_mid_pass(ma, p->rad[d], p->tw[d], 0, p->maxe, stream), "mid pass");
+        KBN_LAUNCH(KBN_CLASS_FFT_MID_FWD, launch_mid(p, d, ma, 0, stream), "mid pass");
         std::swap(cur, nxt);
     }
     *grid = cur;
@@ -709,20 +719,14 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
         ma.inner = (int)inner;
         ma.pad_in = 0;
         ma.crop_out = 1;
-        if (p->fast_fft && kbn_fast_fft_size(p->K[d]))
-            KBN_LAUNCH(KBN_CLASS_FFT_MID_INV, kbn_launch_fast_mid(ma, p->K[d], p->tw[d], 1, stream),
-                       "mid pass");
-        else
-            KBN_LAUNCH(KBN_CLASS_FFT_MID_INV,
-                       kbn_launch_mid_pass(ma, p->rad[d], p->tw[d], 1, p->maxe, stream), "mid pass");
+        KBN_LAUNCH(KBN_CLASS_FFT_MID_INV, launch_mid(p, d, ma, 1, stream), "mid pass");
         std::swap(cur, nxt);
     }
-    // With few image rows per coil, the coil loop inside each line would
-    // leave the GPU idle: then every (image, coil) line is transformed on
-    // its own into the free buffer and the coils are summed afterwards.
-    // The choice depends only on the image shape and coil count, so the
-    // same problem gives the same bits whatever the batch size.
-    const bool split = ncc > 1 && R0 < 2048;
+    // Several coils: every (image, coil) line is transformed on its own into
+    // the free buffer and the coils are summed afterwards.  Summing them in
+    // the pass, line by line, left the GPU idle in 2D (a few dozen workgroups)
+    // and ran at 4 waves per SIMD in 3D.
+    const bool split = ncc > 1;
     KbnLastAdjArgs la;
     la.in = cur;
     la.smaps = smaps ? smaps + (int64_t)c0 * R0 * Nl : nullptr;
@@ -730,7 +734,7 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
     la.nlines = split ? nb * ncc * R0 : nb * R0;
     la.R0 = (int)R0;
     la.Nl = Nl;
-    la.C = split ? 1 : ncc;
+    la.C = 1;
     la.cmod = split ? ncc : 0;
     la.accumulate = (!split && c0 > 0) ? 1 : 0;  // later coil runs add to the image
     la.D = D;
@@ -738,13 +742,7 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
         la.N[d] = p->N[d];
         la.deap[d] = p->deap[d];
     }
-    if (p->fast_fft && kbn_fast_last_size(p->K[D - 1]))
-        KBN_LAUNCH(KBN_CLASS_FFT_LAST_ADJ, kbn_launch_fast_last(la, p->K[D - 1], p->tw[D - 1], stream),
-                   "last adjoint pass");
-    else
-        KBN_LAUNCH(KBN_CLASS_FFT_LAST_ADJ,
-                   kbn_launch_last_adj(la, p->rad[D - 1], p->tw[D - 1], p->maxe, stream),
-                   "last adjoint pass");
+    KBN_LAUNCH(KBN_CLASS_FFT_LAST_ADJ, launch_last(p, la, stream), "last adjoint pass");
     if (split)
         KBN_LAUNCH(KBN_CLASS_FFT_LAST_ADJ,
                    kbn_launch_coil_sum(nxt, nb, ncc, R0 * Nl, x + b0 * R0 * Nl, c0 > 0 ? 1 : 0, stream),
@@ -788,8 +786,8 @@ int run_jac(kbn_plan p, int B, int C, const float2 *img, const float2 *smaps, co
     return run_type2(p, B, C, p->D, 1, img, smaps, 1, nullptr, v, dom, accumulate, stream);
 }
 
-// y = E x and the omega-gradient of run_jac in one pass.  In 2D with the
-// specialised FFT lengths, the first pass (along axis 1) transforms the
+// y = E x and the omega-gradient of run_jac in one pass.  In 2D with grid
+// edges of at least 128 (below, the passes are launch-bound), the first pass (along axis 1) transforms the
 // unweighted and the r^[1]-weighted images only: r^[0] is constant along
 // axis-1 lines, so the axis-0 pass derives the r^[0] channel by scaling the
 // unweighted channel's rows (the persistent pass scales the values it holds
@@ -801,7 +799,7 @@ int run_jac(kbn_plan p, int B, int C, const float2 *img, const float2 *smaps, co
 int run_fwd_jac(kbn_plan p, int B, int C, const float2 *x, const float2 *smaps, float2 *y, const float2 *g,
                 float *dom, int accumulate, hipStream_t stream) {
     const int D = p->D;
-    const bool fuse = D == 2 && p->fast_fft && kbn_fast_fft_size(p->K[0]) && kbn_fast_fft_size(p->K[1]);
+    const bool fuse = D == 2 && p->fast_fft && p->K[0] >= 128 && p->K[1] >= 128;
     if (!fuse) {
         int rc = run_type2(p, B, C, 1, 0, x, smaps, 0, y, nullptr, nullptr, 0, stream);
         return rc == KBN_OK ? run_jac(p, B, C, x, smaps, g, dom, accumulate, stream) : rc;
@@ -838,7 +836,7 @@ int run_fwd_jac(kbn_plan p, int B, int C, const float2 *x, const float2 *smaps, 
             fa.deap[d] = p->deap[d];
         }
         fa.nplain = npair;
-        KBN_LAUNCH(KBN_CLASS_FFT_FIRST, kbn_launch_fast_first(fa, p->K[1], p->tw[1], stream), "first pass");
+        KBN_LAUNCH(KBN_CLASS_FFT_FIRST, launch_first(p, fa, stream), "first pass");
         KbnMidPassArgs ma;
         ma.in = bufA;
         ma.out = bufB;
@@ -850,7 +848,7 @@ int run_fwd_jac(kbn_plan p, int B, int C, const float2 *x, const float2 *smaps, 
         ma.crop_out = 0;
         ma.dsplit = npair;
         ma.dnw = D;
-        KBN_LAUNCH(KBN_CLASS_FFT_MID_FWD, kbn_launch_fast_mid(ma, p->K[0], p->tw[0], 0, stream), "mid pass");
+        KBN_LAUNCH(KBN_CLASS_FFT_MID_FWD, launch_mid(p, 0, ma, 0, stream), "mid pass");
         // the FFT passes overlap the index pass (waiting before the axis-0
         // pass measured 1.79 against 1.76 ms on the 256-image step)
         rc = points_wait(p, stream);
@@ -1104,6 +1102,9 @@ int plan_setup(kbn_plan p, int D, const int64_t *N, const kbn_opts *opts) {
                                                  " outside [2J, " + std::to_string(KBN_MAX_K) + "]");
         p->K[d] = K;
         p->scale[d] = (double)K * (1.0 / (2.0 * M_PI));
+        p->any[d] = kbn_any_passes(K);
+        if (!p->any[d].first && !(kbn_fast_rows_size(K) && kbn_fast_cols_size(K)))
+            return fail(KBN_ERR_UNSUPPORTED, "no FFT passes for K_d = " + std::to_string(K));
         if (!factor(K, p->rad[d])) return fail(KBN_ERR_UNSUPPORTED, "K_d not 7-smooth");
     }
     // sorting / gather tiles; the automatic size grows until the tile count
