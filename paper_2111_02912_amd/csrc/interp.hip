@@ -31,14 +31,14 @@ namespace {
 // one tile).  Channels are taken CP at a time (CP = 2 or 4): their grid
 // regions (tile plus the tap reach) are loaded into LDS interleaved, with
 // coalesced reads, and every thread interpolates its point for all CP
-// channels from LDS, one 16-byte read per tap and channel pair.  With LA the
-// region of the next CP channels is loaded into registers while the current
-// ones are interpolated (each thread keeps the grid offsets of its region
-// cells, computed once), so the grid reads overlap the interpolation.  Subproblems
+// channels from LDS, one 16-byte read per tap and channel pair.  With MAXC > 0
+// the region of the next CP channels is loaded into registers while the
+// current ones are interpolated (at most MAXC cells per thread, whose grid
+// offsets are computed once), so the grid reads overlap the interpolation.  Subproblems
 // of the extra tile id ntiles hold the flagged points, whose outputs are NaN.
 // Body of one workgroup: subproblem s, channel group gy (the kernel's
 // blockIdx.x and blockIdx.y), regions staged in reg4.
-template <int D, int J, int MODE, int CP, bool LA>
+template <int D, int J, int MODE, int CP, int MAXC>
 __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGatherArgs &a, int cg, int s, int gy,
                                                  float4 *reg4) {
     constexpr int H = CP / 2;  // float4 (channel pairs) per region cell
@@ -100,13 +100,14 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
     float jac[KBN_MAX_D] = {0.f, 0.f, 0.f};
     // LA: region cells of this thread and their grid offsets (the same for
     // every channel), and the next channel group's region loaded ahead
-    constexpr int MAXC = LA ? (48 * 1024 / (CP * 8) + KBN_BLOCK - 1) / KBN_BLOCK : 1;
-    int goff[MAXC];
-    float4 pre[MAXC][H];
+    constexpr bool LA = MAXC > 0;
+    constexpr int NCELL = LA ? MAXC : 1;
+    int goff[NCELL];
+    float4 pre[NCELL][H];
     auto fetch = [&](int chb) {
         const int nc = min(CP, ch1 - chb);
 #pragma unroll
-        for (int k = 0; k < MAXC; ++k) {
+        for (int k = 0; k < NCELL; ++k) {
             const int i = (int)threadIdx.x + k * KBN_BLOCK;
 #pragma unroll
             for (int h = 0; h < H; ++h) {
@@ -121,7 +122,7 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
     };
     if constexpr (LA) {
 #pragma unroll
-        for (int k = 0; k < MAXC; ++k) {
+        for (int k = 0; k < NCELL; ++k) {
             const int i = (int)threadIdx.x + k * KBN_BLOCK;
             int rem = i < R ? i : 0;
             int gi = 0, gstride = 1;
@@ -140,7 +141,7 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
         const int nc = min(CP, ch1 - ch);
         if constexpr (LA) {
 #pragma unroll
-            for (int k = 0; k < MAXC; ++k) {
+            for (int k = 0; k < NCELL; ++k) {
                 const int i = (int)threadIdx.x + k * KBN_BLOCK;
                 if (i < R) {
 #pragma unroll
@@ -291,16 +292,31 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
     }
 }
 
-template <int D, int J, int MODE, int CP, bool LA>
+// Workgroup x -> subproblem: consecutive workgroups go to the 8 XCDs in turn,
+// so runs of KBN_XCD_RUN consecutive subproblems are dealt to one XCD at a
+// time; the regions of a split tile and of neighbouring tiles then meet in
+// one L2 while the runs stay short enough to balance the XCDs (96^3 x 8
+// channels: 2.6 -> 1.2 GB fetched, 434 -> 402 us; 256^2 x 256: 1.17 -> 0.67 GB,
+// 195 -> 186 us; runs of 4 the same, of 32 and whole-XCD ranges slower).
+#define KBN_XCD_RUN 8
+__host__ __device__ inline int64_t xcd_padded(int64_t n) {
+    return (n + 8 * KBN_XCD_RUN - 1) / (8 * KBN_XCD_RUN) * (8 * KBN_XCD_RUN);
+}
+__device__ __forceinline__ int xcd_run_index(int x) {
+    const int q = x >> 3;
+    return ((q / KBN_XCD_RUN) * 8 + (x & 7)) * KBN_XCD_RUN + q % KBN_XCD_RUN;
+}
+
+template <int D, int J, int MODE, int CP, int MAXC>
 __global__ void __launch_bounds__(KBN_BLOCK) k_gather_staged(KbnGeom g, KbnGatherArgs a, int cg) {
     extern __shared__ float4 reg4[];
-    gather_staged_wg<D, J, MODE, CP, LA>(g, a, cg, blockIdx.x, blockIdx.y, reg4);
+    gather_staged_wg<D, J, MODE, CP, MAXC>(g, a, cg, xcd_run_index(blockIdx.x), blockIdx.y, reg4);
 }
 
 // The staged gathers of several plans in one launch: workgroup w belongs to
 // the job i with start[i] <= w < start[i + 1] and is that job's workgroup
 // (w - start[i]) mod blocks of channel group (w - start[i]) / blocks.
-template <int D, int J, int MODE, int CP, bool LA>
+template <int D, int J, int MODE, int CP, int MAXC>
 __global__ void __launch_bounds__(KBN_BLOCK)
 k_gather_multi(const KbnGatherJob *__restrict__ jobs, const int64_t *__restrict__ start, int njobs) {
     extern __shared__ float4 reg4[];
@@ -313,7 +329,7 @@ k_gather_multi(const KbnGatherJob *__restrict__ jobs, const int64_t *__restrict_
     }
     const KbnGatherJob &j = jobs[lo];
     const int64_t local = w - start[lo];
-    gather_staged_wg<D, J, MODE, CP, LA>(j.g, j.a, j.cg, (int)(local % j.blocks), (int)(local / j.blocks), reg4);
+    gather_staged_wg<D, J, MODE, CP, MAXC>(j.g, j.a, j.cg, (int)(local % j.blocks), (int)(local / j.blocks), reg4);
 }
 
 // Direct gather (no staging): one thread per sorted point reads its taps from
@@ -1208,9 +1224,11 @@ k_reduce_parts(float *__restrict__ dst, const float *__restrict__ part, int64_t 
 
 }  // namespace
 
-// About KBN_GATHER_WG_TARGET workgroups over point blocks x groups (1024
-// and fixed groups of 16, 24 or 32 channel sets measured slower on the
-// 256-image step; 16 sets gained 4% on the 8-coil training step).
+// About KBN_GATHER_WG_TARGET workgroups over point blocks x groups: five are
+// resident per CU, and their durations differ with the points they hold, so
+// several rounds of them even out (256^2 x 256 channels, forward and
+// omega-Jacobian: 2048 177 and 285 us, 4096 161 and 262, 8192 157 and 249, more
+// the same; fewer than 2048 is slower from 64 channels on).
 int64_t kbn_gather_groups(int64_t blocks, int64_t nbc) {
     return std::max<int64_t>(1, std::min<int64_t>(nbc, (KBN_GATHER_WG_TARGET + blocks - 1) / blocks));
 }
@@ -1237,6 +1255,7 @@ KbnGatherShape kbn_gather_shape(const KbnGeom &g, int64_t M, int nch, int nw) {
     sh.blocks = blocks;
     const int64_t groups = kbn_gather_groups(blocks, nbc);
     sh.cg = (int)(((nbc + groups - 1) / groups) * nw);
+    if (nw == 1) sh.cg += sh.cg & 1;  // whole channel pairs: 8 channels one by one 21 us, in pairs 16 us
     sh.groups = (nch + sh.cg - 1) / sh.cg;
     return sh;
 }
@@ -1258,13 +1277,30 @@ hipError_t gather_dj(const KbnGeom &g, const KbnGatherArgs &a, int mode, hipStre
     const KbnGatherShape sh = kbn_gather_shape(g, a.M, a.nch, a.nw);
     dim3 grid((unsigned)sh.blocks, (unsigned)sh.groups);
     if (sh.staged) {
-        // loading ahead pays in 3D (96^3 x 8 coils: 11-14%); in 2D it cost
-        // occupancy for no gain in the full step
-        constexpr bool LA = D == 3;
-        if (mode == 0)
-            k_gather_staged<D, J, 0, 2, LA><<<grid, dim3(KBN_BLOCK), sh.lds, s>>>(g, a, sh.cg);
-        else
-            k_gather_staged<D, J, 1, 2, LA><<<grid, dim3(KBN_BLOCK), sh.lds, s>>>(g, a, sh.cg);
+        grid.x = (unsigned)xcd_padded(sh.blocks);
+        // region cells per thread, loaded ahead in registers: the default
+        // tiles' 37^2 (6) and 13^3 (9, or 10 with an edge of 9), in 3D up to
+        // the 12 of 48 KiB.  Measured in 2D against loading them between the
+        // barriers: 256^2 x 256 channels 184 -> 177 us and 311 -> 284 us
+        // (omega-Jacobian), 320^2 x 64 channels 73 -> 58 and 161 -> 126 us
+        const int64_t cells = ((int64_t)(sh.lds / (sh.cp * sizeof(float2))) + KBN_BLOCK - 1) / KBN_BLOCK;
+#define KBN_GATHER(c)                                                                              \
+    do {                                                                                           \
+        if (mode == 0)                                                                             \
+            k_gather_staged<D, J, 0, 2, c><<<grid, dim3(KBN_BLOCK), sh.lds, s>>>(g, a, sh.cg);     \
+        else                                                                                       \
+            k_gather_staged<D, J, 1, 2, c><<<grid, dim3(KBN_BLOCK), sh.lds, s>>>(g, a, sh.cg);     \
+    } while (0)
+        if (D == 2) {
+            if (cells <= 6) KBN_GATHER((D == 2 ? 6 : 0));
+            else KBN_GATHER(0);
+        } else if (D == 3) {
+            if (cells <= 10) KBN_GATHER((D == 3 ? 10 : 0));
+            else KBN_GATHER((D == 3 ? 12 : 0));
+        } else {
+            KBN_GATHER(0);
+        }
+#undef KBN_GATHER
     } else {
         if (mode == 0)
             k_gather<D, J, 0><<<grid, dim3(KBN_BLOCK), 0, s>>>(g, a, sh.cg);
@@ -1282,12 +1318,12 @@ hipError_t gather_dj(const KbnGeom &g, const KbnGatherArgs &a, int mode, hipStre
 template <int D, int J>
 hipError_t gather_multi_dj(int mode, const KbnGatherJob *jobs, const int64_t *start, int njobs, int64_t total,
                            size_t lds, hipStream_t s) {
-    constexpr bool LA = D == 3;
+    constexpr int MAXC = D == 3 ? 12 : 0;  // any staged region (48 KiB)
     const dim3 grid((unsigned)total);
     if (mode == 0)
-        k_gather_multi<D, J, 0, 2, LA><<<grid, dim3(KBN_BLOCK), lds, s>>>(jobs, start, njobs);
+        k_gather_multi<D, J, 0, 2, MAXC><<<grid, dim3(KBN_BLOCK), lds, s>>>(jobs, start, njobs);
     else
-        k_gather_multi<D, J, 1, 2, LA><<<grid, dim3(KBN_BLOCK), lds, s>>>(jobs, start, njobs);
+        k_gather_multi<D, J, 1, 2, MAXC><<<grid, dim3(KBN_BLOCK), lds, s>>>(jobs, start, njobs);
     return hipGetLastError();
 }
 
