@@ -353,13 +353,15 @@ void kbn_internal_phase_release(KbnPhased *ph, hipStream_t s);
 #define KBN_CG_BETA 4
 #define KBN_CG_REL 5
 #define KBN_CG_ITERS 6
+#define KBN_CG_RRPREV 8   // rr of the iteration before (internal)
 #define KBN_CG_NSCAL 32
 #define KBN_CG_MAXPARTS 1024
+#define KBN_CG_PARTS (2 * KBN_CG_MAXPARTS)  // <p, q> partials, then |r|^2 partials
 // kernel groups of one CG step
 #define KBN_CGK_INIT 0  // x = 0, p = r, rr = bb = |r|^2
-#define KBN_CGK_Q 1     // q += lambda T^H T p, alpha = rr / <p, q>
-#define KBN_CGK_XR 2    // x += alpha p, r -= alpha q, beta, rr, rel
-#define KBN_CGK_P 3     // p = r + beta p
+#define KBN_CGK_Q 1     // q = sum of the coil images src + lambda T^H T p
+#define KBN_CGK_XR 2    // alpha = rr / <p, q>, x += alpha p, r -= alpha q
+#define KBN_CGK_P 3     // beta, rr, rel, p = r + beta p
 int kbn_cg_nparts(int64_t n);
 
 // ---------------------------------------------------------------------------
@@ -381,5 +383,6 @@ struct KbnCgImage {
     int n0, n1, n2;
 };
 #define KBN_CG_MAXB 65535  // images per CG launch (grid rows)
-hipError_t kbn_launch_cg(int kind, int nimg, int64_t n, float2 *x, float2 *r, float2 *p, float2 *q,
-                         float lam, KbnCgImage img, double *scal, double *part, hipStream_t s);
+// src, C (KBN_CGK_Q): the C coil images of every image's E^H E p, or q with C = 1
+hipError_t kbn_launch_cg(int kind, int nimg, int64_t n, float2 *x, float2 *r, float2 *p, float2 *q, const float2 *src,
+                         int C, float lam, KbnCgImage img, double *scal, double *part, hipStream_t s);

@@ -699,8 +699,11 @@ KbnSpreadArgs t1_spread_args(kbn_plan p, int64_t nch, const float2 *y_chunk, flo
 // Inverse FFT passes of one adjoint chunk whose spread grids are in bufA:
 // strided passes with cropping, then the last-axis pass with cropping,
 // scaling and conj(coil map), summed over the chunk's coils into x.
+// With coil_images the coil sum is left to the caller: the chunk's coil images
+// [nb][ncc] stay in the workspace and *coil_images points to them (or stays
+// null when there is a single coil, whose image is in x).
 int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 *smaps, float2 *x, float2 *bufA,
-              float2 *bufB, hipStream_t stream) {
+              float2 *bufB, hipStream_t stream, const float2 **coil_images = nullptr) {
     const int D = p->D;
     const int64_t R0 = img_rows(p);
     const int Nl = p->N[D - 1];
@@ -743,7 +746,9 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
         la.deap[d] = p->deap[d];
     }
     KBN_LAUNCH(KBN_CLASS_FFT_LAST_ADJ, launch_last(p, la, stream), "last adjoint pass");
-    if (split)
+    if (split && coil_images)
+        *coil_images = nxt;
+    else if (split)
         KBN_LAUNCH(KBN_CLASS_FFT_LAST_ADJ,
                    kbn_launch_coil_sum(nxt, nb, ncc, R0 * Nl, x + b0 * R0 * Nl, c0 > 0 ? 1 : 0, stream),
                    "coil sum");
@@ -751,9 +756,10 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
 }
 
 // Adjoint pipeline: spread, inverse FFT passes with cropping, scaling and
-// conj(coil map) summed over coils.
+// conj(coil map) summed over coils.  With coil_images (see t1_passes) the sum
+// is left to the caller where the whole batch is one chunk.
 int run_type1(kbn_plan p, int B, int C, const float2 *y, const float2 *smaps, float2 *x,
-              hipStream_t stream) {
+              hipStream_t stream, const float2 **coil_images = nullptr) {
     const int64_t gsz = p->gsize();
     const int64_t per_coil = type1_per_coil(p, p->M);
     const Chunks ck = split_chunks(B, C, per_coil, p->max_ws);
@@ -773,7 +779,8 @@ int run_type1(kbn_plan p, int B, int C, const float2 *y, const float2 *smaps, fl
         const int64_t nch = nb * ncc;
         const KbnSpreadArgs sa = t1_spread_args(p, nch, y + (b0 * C + c0) * p->M, bufA, bufY, bufP);
         KBN_LAUNCH(KBN_CLASS_SPREAD, kbn_launch_spread(geom, sa, stream), "spread");
-        rc = t1_passes(p, b0, c0, nb, ncc, smaps, x, bufA, bufB, stream);
+        rc = t1_passes(p, b0, c0, nb, ncc, smaps, x, bufA, bufB, stream,
+                       ck.bc == B && ck.cc == C ? coil_images : nullptr);
         if (rc != KBN_OK) return rc;
     }
     return KBN_OK;
@@ -1436,7 +1443,7 @@ int kbn_jac_x(kbn_plan p, int op, int B, int C, const void *g, const void *smaps
 }
 
 // CG work buffer for B images: scalars [B][KBN_CG_NSCAL], block partials
-// [B][KBN_CG_MAXPARTS], r, p, q (images [B][N..]), E p (k-space [B][C][M])
+// [B][KBN_CG_PARTS], r, p, q (images [B][N..]), E p (k-space [B][C][M])
 struct CgBufs {
     double *scal, *part;
     float2 *r, *p, *q, *ytmp;
@@ -1448,7 +1455,7 @@ static int64_t cg_bytes(kbn_plan p, int B, int C, CgBufs *b, void *work) {
     int64_t npix = 1;
     for (int d = 0; d < p->D; ++d) npix *= p->N[d];
     const int64_t o_part = cg_align((int64_t)B * KBN_CG_NSCAL * 8);
-    const int64_t o_r = o_part + cg_align((int64_t)B * KBN_CG_MAXPARTS * 8);
+    const int64_t o_r = o_part + cg_align((int64_t)B * KBN_CG_PARTS * 8);
     const int64_t img = cg_align((int64_t)B * npix * 8);
     const int64_t o_y = o_r + 3 * img;
     const int64_t total = o_y + cg_align(std::max<int64_t>(p->M, 0) * C * B * 8);
@@ -1465,11 +1472,12 @@ static int64_t cg_bytes(kbn_plan p, int B, int C, CgBufs *b, void *work) {
 }
 
 static int cg_launch(kbn_plan p, int kind, int B, int64_t n, float2 *x, const CgBufs &b, float lam, int reg,
-                     hipStream_t s) {
+                     hipStream_t s, const float2 *src = nullptr, int C = 1) {
     KbnCgImage img{reg, 1, 1, 1};
     int *ext[3] = {&img.n0, &img.n1, &img.n2};
     for (int d = 0; d < p->D; ++d) *ext[d] = (int)p->N[d];
-    return launched(kbn_launch_cg(kind, B, n, x, b.r, b.p, b.q, lam, img, b.scal, b.part, s),
+    return launched(kbn_launch_cg(kind, B, n, x, b.r, b.p, b.q, src ? src : b.q, src ? C : 1, lam, img, b.scal,
+                                  b.part, s),
                     "cg vector kernel", s);
 }
 
@@ -1546,9 +1554,10 @@ int kbn_cg_step(kbn_plan p, int B, int C, const void *smaps, double lambda, int 
                            stream);
             if (rc != KBN_OK) return rc;
         }
-        rc = run_type1(p, B, C, b.ytmp, (const float2 *)smaps, b.q, stream);
+        const float2 *coils = nullptr;
+        rc = run_type1(p, B, C, b.ytmp, (const float2 *)smaps, b.q, stream, &coils);
         if (rc != KBN_OK) return rc;
-        rc = cg_launch(p, KBN_CGK_Q, B, npix, (float2 *)x, b, (float)lambda, reg, stream);
+        rc = cg_launch(p, KBN_CGK_Q, B, npix, (float2 *)x, b, (float)lambda, reg, stream, coils, C);
         if (rc == KBN_OK) rc = cg_launch(p, KBN_CGK_XR, B, npix, (float2 *)x, b, 0.f, reg, stream);
         if (rc == KBN_OK) rc = cg_launch(p, KBN_CGK_P, B, npix, (float2 *)x, b, 0.f, reg, stream);
         if (rc != KBN_OK) return rc;

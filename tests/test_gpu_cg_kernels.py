@@ -1,0 +1,67 @@
+"""The CG iteration's vector kernels against the same iteration in FP64.
+
+Both sides apply the library's operator to their own search directions, so
+they differ by the FP32 rounding of x, r, p and q (6e-8 relative per update)
+and of the operator on directions that differ by that much.  lambda is of
+the size of the largest eigenvalues of E^H E, which keeps the growth over
+three iterations well below 100 roundings: 6e-6.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2111_02912_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TOL = 6e-6
+
+
+# one block and several per image, a length past one pass of the grid's 1024
+# blocks, one coil (no coil sum), coils and images in one run and in several
+# (bytes of workspace), an axis of odd length
+@pytest.mark.parametrize("N,M,B,C,reg,ws", [
+    ((12,), 40, 1, 1, "identity", 0), ((15, 17), 400, 1, 2, "identity", 0), ((15, 17), 400, 3, 5, "finite_diff", 0),
+    ((40, 36), 2000, 2, 3, "identity", 1), ((40, 36), 2000, 2, 3, "finite_diff", 200000),
+    ((512, 512), 6000, 1, 2, "finite_diff", 0), ((100, 60, 50), 6000, 1, 2, "identity", 0), ((9, 12, 10), 900, 2, 4, "identity", 0),
+])
+def test_cg_iterations_match_fp64_vectors(N, M, B, C, reg, ws):
+    from paper_2111_02912_amd.cg import cg_sense
+    from paper_2111_02912_amd.nufft import KbNufft
+    print(f"cg kernels N={N} M={M} B={B} C={C} {reg} workspace={ws}", flush=True)
+    dev = torch.device("cuda", 0)
+    plan = KbNufft(N, device=dev, max_workspace=ws)
+    plan.set_points(torch.from_numpy(W.uniform_random(M, len(N), seed=51)).to(dev))
+    smaps = torch.from_numpy(W.sense_maps(C, N)).to(dev) if C > 1 else None
+    y = torch.from_numpy(W.complex_normal((B, C, M), 52)).to(dev)
+    lam = float(max(M, np.prod(N)))
+    x, rel = cg_sense(plan, y, smaps, lam=lam, iters=3, reg=reg)
+
+    def lap(v):
+        if reg == "identity":
+            return v
+        out = torch.zeros_like(v)
+        for d in range(1, v.dim()):
+            g = torch.diff(v, dim=d)
+            n = v.shape[d]
+            out.narrow(d, 1, n - 1).add_(g)
+            out.narrow(d, 0, n - 1).sub_(g)
+        return out
+
+    def dot(a, b):
+        return (a.conj() * b).real.flatten(1).sum(1).view(B, *[1] * len(N))
+
+    r = plan.adjoint(y, smaps).to(torch.complex128)
+    p, xr, bb = r.clone(), torch.zeros_like(r), dot(r, r)
+    rr = bb
+    for _ in range(3):
+        q = plan.adjoint(plan.forward(p.to(torch.complex64), smaps), smaps).to(torch.complex128) + lam * lap(p)
+        a = rr / dot(p, q)
+        xr, r = xr + a * p, r - a * q
+        rn = dot(r, r)
+        p, rr = r + rn / rr * p, rn
+    err = (x - xr).flatten(1).norm(dim=1) / xr.flatten(1).norm(dim=1)
+    res = (rr / bb).sqrt().flatten()
+    print("  ", err.max().item(), flush=True)
+    assert err.max().item() < TOL
+    assert torch.allclose(rel.double().cpu().flatten(), res.cpu(), rtol=100 * TOL, atol=TOL)
