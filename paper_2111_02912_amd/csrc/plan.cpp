@@ -190,13 +190,18 @@ struct kbn_plan_s {
     // The index pass runs on a stream of the plan's own, beside the caller's
     // stream, so that a forward call's FFT passes (which do not read the
     // points) overlap it; every read of the point buffers first makes its
-    // stream wait for points_ready.
+    // stream wait: the gathers for the sorted samples (points_sorted), all
+    // else for the whole pass (points_ready), whose second half, the spread's
+    // owner lists, thus runs beside the gathers (3D 75 x 90 x 64, M = 150000:
+    // 0.24 of the pass's 0.37 ms; the training step 1167 -> 1080 us).
     hipStream_t istream = nullptr;
-    hipEvent_t points_in = nullptr, points_ready = nullptr, omega_read = nullptr;
+    hipEvent_t points_in = nullptr, points_sorted = nullptr, points_ready = nullptr, omega_read = nullptr;
     bool points_pending = false;
     uint64_t points_gen = 0;               // index passes issued
     hipStream_t waited_stream = nullptr;   // the last stream ordered after pass waited_gen
     uint64_t waited_gen = 0;
+    hipStream_t sorted_stream = nullptr;   // likewise, after its sort at least
+    uint64_t sorted_gen = 0;
     int D = 0;
     int N[KBN_MAX_D] = {1, 1, 1};
     int K[KBN_MAX_D] = {1, 1, 1};
@@ -360,7 +365,7 @@ void free_points(kbn_plan p, hipStream_t s) {
     p->counts_cap = 0;
 }
 
-int points_wait(kbn_plan p, hipStream_t stream);
+int points_wait(kbn_plan p, hipStream_t stream, bool sorted_only = false);
 
 void free_plan(kbn_plan p, hipStream_t s) {
     (void)points_wait(p, s);  // the frees below come after the last index pass
@@ -388,6 +393,7 @@ void free_plan(kbn_plan p, hipStream_t s) {
     if (p->points_in) (void)hipEventDestroy(p->points_in);
     if (p->omega_read) (void)hipEventDestroy(p->omega_read);
     if (p->points_ready) (void)hipEventDestroy(p->points_ready);
+    if (p->points_sorted) (void)hipEventDestroy(p->points_sorted);
     if (p->istream) (void)hipStreamDestroy(p->istream);
     if (p->upload_done) {
         if (hipEventQuery(p->upload_done) != hipSuccess) (void)hipEventSynchronize(p->upload_done);
@@ -396,24 +402,26 @@ void free_plan(kbn_plan p, hipStream_t s) {
     delete p;
 }
 
-// Orders `stream` after the plan's last index pass.  Under graph capture
+// Orders `stream` after the plan's last index pass (sorted_only: after its
+// sorted samples, which is all that a gather reads).  Under graph capture
 // the wait would be on an event recorded outside the capture, so a capture
 // requires the index pass to be known finished (kbn_check_error, or the
 // batch capture's own eager pass); captured plans refuse new points.
-int points_wait(kbn_plan p, hipStream_t stream) {
+int points_wait(kbn_plan p, hipStream_t stream, bool sorted_only) {
     if (!p->points_pending) return KBN_OK;
     // a stream already ordered after this pass needs no second wait (the
     // launch-bound small problems issue dozens of calls per pass)
     if (p->waited_gen == p->points_gen && p->waited_stream == stream) return KBN_OK;
+    if (sorted_only && p->sorted_gen == p->points_gen && p->sorted_stream == stream) return KBN_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) != hipSuccess) return fail(KBN_ERR_HIP, "hipStreamIsCapturing");
     if (cs != hipStreamCaptureStatusNone)  // (no event query either: not allowed in every capture mode)
         return fail(KBN_ERR_UNSUPPORTED,
                     "capture while the index pass of kbn_set_points may still run: call kbn_check_error first");
-    if (hipStreamWaitEvent(stream, p->points_ready, 0) != hipSuccess)
+    if (hipStreamWaitEvent(stream, sorted_only ? p->points_sorted : p->points_ready, 0) != hipSuccess)
         return fail(KBN_ERR_HIP, "hipStreamWaitEvent (points)");
-    p->waited_stream = stream;
-    p->waited_gen = p->points_gen;
+    (sorted_only ? p->sorted_stream : p->waited_stream) = stream;
+    (sorted_only ? p->sorted_gen : p->waited_gen) = p->points_gen;
     return KBN_OK;
 }
 
@@ -658,7 +666,7 @@ int run_type2(kbn_plan p, int B, int C, int nw, int weighted, const float2 *x,
         const int64_t nch = nb * ncc * nw;
         float2 *grid = nullptr;
         int rc = t2_passes(p, nw, weighted, x, smaps, b0, c0, nb, ncc, bufA, bufB, &grid, stream);
-        if (rc == KBN_OK) rc = points_wait(p, stream);  // the FFT passes overlap the index pass
+        if (rc == KBN_OK) rc = points_wait(p, stream, true);  // the FFT passes overlap the index pass
         if (rc != KBN_OK) return rc;
         const KbnGatherArgs ga = t2_gather_args(p, nch, ncc, nw, mode, grid, (b0 * C + c0) * p->M, y, v, dom, part,
                                                 (accumulate || b0 > 0 || c0 > 0) ? 1 : 0);
@@ -858,7 +866,7 @@ int run_fwd_jac(kbn_plan p, int B, int C, const float2 *x, const float2 *smaps, 
         KBN_LAUNCH(KBN_CLASS_FFT_MID_FWD, launch_mid(p, 0, ma, 0, stream), "mid pass");
         // the FFT passes overlap the index pass (waiting before the axis-0
         // pass measured 1.79 against 1.76 ms on the 256-image step)
-        rc = points_wait(p, stream);
+        rc = points_wait(p, stream, true);
         if (rc != KBN_OK) return rc;
         const int64_t k0 = (b0 * C + c0) * p->M;
         const KbnGatherArgs gy = t2_gather_args(p, npair, ncc, 1, 0, bufB, k0, y, nullptr, nullptr, nullptr, 0);
@@ -1199,6 +1207,8 @@ int index_pass(kbn_plan p, int64_t M, const float *omega, const KbnPointsBufs &b
                kbn_launch_points(p->D, M, omega, p->scale, p->K, p->T, p->nt, p->ntiles, p->ntiles_own, p->sub, b,
                                  stream, stream == p->istream ? p->omega_read : nullptr),
                "index pass");
+    if (stream == p->istream && hipEventRecord(p->points_sorted, stream) != hipSuccess)
+        return fail(KBN_ERR_HIP, "index stream order");
     KBN_LAUNCH(KBN_CLASS_INDEX,
                kbn_launch_owner_lists(p->geom(), M, p->cell, p->frac, p->toff, p->order,
                                       p->counts + kbn_points_owner_base(M, p->ntiles), p->ooff, p->otile_order,
@@ -1274,6 +1284,7 @@ int kbn_plan_create(kbn_plan *out, int D, const int64_t *N, const kbn_opts *opts
         rc = fail(KBN_ERR_HIP, "upload event");
     if (rc == KBN_OK && (hipStreamCreateWithFlags(&p->istream, hipStreamNonBlocking) != hipSuccess ||
                          hipEventCreateWithFlags(&p->points_in, hipEventDisableTiming) != hipSuccess ||
+                         hipEventCreateWithFlags(&p->points_sorted, hipEventDisableTiming) != hipSuccess ||
                          hipEventCreateWithFlags(&p->points_ready, hipEventDisableTiming) != hipSuccess ||
                          hipEventCreateWithFlags(&p->omega_read, hipEventDisableTiming) != hipSuccess))
         rc = fail(KBN_ERR_HIP, "index stream");

@@ -1,0 +1,47 @@
+"""Calls issued right behind kbn_set_points, whose index pass is still
+running beside them: the gathers start after its sort, the spreads after its
+owner lists.  Every result has the bits of the same call on a plan whose pass
+is known to have ended."""
+import pytest
+import torch
+
+from paper_2111_02912_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+# above and below the number of points from which the pass has its own stream
+@pytest.mark.parametrize("N,Ms", [((96, 80), (8192, 60000, 500, 9000)), ((24, 30, 20), (30000, 8192, 100, 40000))])
+@pytest.mark.parametrize("other_stream", [False, True])
+def test_calls_behind_set_points(N, Ms, other_stream):
+    from paper_2111_02912_amd.nufft import KbNufft
+    dev = torch.device("cuda", 0)
+    plan = KbNufft(N, device=dev)
+    x = torch.from_numpy(W.complex_normal((1,) + tuple(N), 61)).to(dev)
+    side = torch.cuda.Stream(dev)
+    got, want, sets = [], [], []
+    for k, M in enumerate(Ms):
+        om = torch.from_numpy(W.uniform_random(M, len(N), seed=62 + k)).to(dev)
+        y = torch.from_numpy(W.complex_normal((1, 1, M), 70 + k)).to(dev)
+        sets.append((om, y))
+    torch.cuda.synchronize()
+    for om, y in sets:
+        print(f"set points N={N} M={om.shape[0]} other_stream={other_stream}", flush=True)
+        plan.set_points(om)
+        f = plan.forward(x)
+        if other_stream:
+            side.wait_stream(torch.cuda.current_stream(dev))
+            with torch.cuda.stream(side):
+                a = plan.adjoint(y)
+            torch.cuda.current_stream(dev).wait_stream(side)
+        else:
+            a = plan.adjoint(y)
+        got.append((f, a, *plan.forward_jac_omega(x, y)))
+    torch.cuda.synchronize()
+    for om, y in sets:
+        q = KbNufft(N, device=dev).set_points(om)
+        q.check_error()
+        want.append((q.forward(x), q.adjoint(y), *q.forward_jac_omega(x, y)))
+    torch.cuda.synchronize()
+    for g, w in zip(got, want):
+        assert all(torch.equal(a, b) for a, b in zip(g, w))
