@@ -27,6 +27,9 @@
 
 namespace {
 
+// index in the k-space array of the sample at sorted position p
+__device__ __forceinline__ int sample_index(const int *order, int64_t p) { return order ? order[p] : (int)p; }
+
 // Staged gather: one workgroup per subproblem (<= KBN_SUB sorted points of
 // one tile).  Channels are taken CP at a time (CP = 2 or 4): their grid
 // regions (tile plus the tap reach) are loaded into LDS interleaved, with
@@ -51,7 +54,7 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
     if (tile == g.ntiles) {  // flagged points
         const int p = p0 + threadIdx.x;
         if (p < a.M) {
-            const int q = a.order[p];
+            const int q = sample_index(a.order, p);
             if (MODE == 0) {
                 for (int ch = ch0; ch < ch1; ++ch) a.y[(int64_t)ch * a.M + q] = make_float2(qnan, qnan);
             } else {
@@ -85,7 +88,7 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
     float w[D][J];
     int base = 0;  // region offset of the point's first tap
     if (act) {
-        q = a.order[p];
+        q = sample_index(a.order, p);
         int stride = 1;
 #pragma unroll
         for (int d = D - 1; d >= 0; --d) {
@@ -338,7 +341,7 @@ template <int D, int J, int MODE>
 __global__ void __launch_bounds__(KBN_BLOCK) k_gather(KbnGeom g, KbnGatherArgs a, int cg) {
     const int64_t p = (int64_t)blockIdx.x * KBN_BLOCK + threadIdx.x;
     if (p >= a.M) return;
-    const int q = a.order[p];
+    const int q = sample_index(a.order, p);
     const bool bad = p >= a.toff[g.ntiles];
     float w[D][J];
     int idx[D][J];
@@ -881,9 +884,11 @@ __global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5) k_spread_mf2(KbnGeom
     };
     auto stage = [&](float *buf, int n) {
 #pragma unroll
-        for (int p = 0; p < TP; ++p)
+        for (int p = 0; p < TP; ++p) {
+            if (16 * p >= n) break;  // (no step reads these records)
             buf[(te + 16 * p) * STR + wpos] =
                 cell_weight<J>(tap_poly(cf, __int_as_float(t[p].y)), t[p].x, cc, Kx, te + 16 * p < n);
+        }
 #pragma unroll
         for (int r = 0; r < YF; ++r)
             *reinterpret_cast<float2 *>(buf + ty * STR + 16 + 2 * (kb + 256 / EB * r)) =
@@ -972,7 +977,7 @@ k_permute_groups(const float2 *__restrict__ y, float2 *__restrict__ ys, const in
     const int64_t p = i / w;
     if (p >= M) return;
     const int c = (int)(i - p * w);
-    ys[(int64_t)ch0 * M + i] = y[(int64_t)(ch0 + c) * M + order[p]];
+    ys[(int64_t)ch0 * M + i] = y[(int64_t)(ch0 + c) * M + sample_index(order, p)];
 }
 
 // 3D: a workgroup of 8 / S * CS waves per (work item, 8 / S channels), each
@@ -1151,13 +1156,17 @@ __global__ void __launch_bounds__(512 / S * CS, S == 2 ? 5 : 6) k_spread_mf3(Kbn
 
 // Tiles split into several work items: sum their partial tiles in slot
 // order (deterministic) and write the grid tile.  Block = (channel, tile).
+// Bound by its chain of loads (4 us whatever the grid, with 64 tiles or none):
+// the first tile's entry is read beside the count that says whether it exists.
 template <int D>
 __global__ void __launch_bounds__(KBN_BLOCK) k_spread_combine(KbnGeom g, KbnSpreadArgs a) {
     const int ncomb = a.scounts[1];
     const int ch = blockIdx.x;
     float2 *G = a.grid + (int64_t)ch * a.gsize;
-    for (int k = blockIdx.y; k < ncomb; k += gridDim.y) {
-        const int tile = a.scomb[3 * k], slot0 = a.scomb[3 * k + 1], ns = a.scomb[3 * k + 2];
+    int k = blockIdx.y;  // < ncomb_max
+    int tile = a.scomb[3 * k], slot0 = a.scomb[3 * k + 1], ns = a.scomb[3 * k + 2];
+    for (; k < ncomb; k += gridDim.y) {
+        if (k != (int)blockIdx.y) tile = a.scomb[3 * k], slot0 = a.scomb[3 * k + 1], ns = a.scomb[3 * k + 2];
         int a0[KBN_MAX_D], te[KBN_MAX_D];
         int rem = tile;
         for (int d = D - 1; d >= 0; --d) {
@@ -1208,7 +1217,7 @@ k_permute(const float2 *__restrict__ y, float2 *__restrict__ ys, const int *__re
     const int64_t p = (int64_t)blockIdx.x * KBN_BLOCK + threadIdx.x;
     if (p >= M) return;
     const int64_t ch = blockIdx.y;
-    ys[ch * M + p] = y[ch * M + order[p]];
+    ys[ch * M + p] = y[ch * M + sample_index(order, p)];
 }
 
 // dst[i] = (accumulate ? dst[i] : 0) + sum_g part[g][i], summed in group order.

@@ -209,7 +209,7 @@ struct KbnGatherArgs {
     int nch;                   // channels in this chunk
     int C, nw;                 // channel = (b_local * C + c) * nw + w
     int64_t M;
-    const int *order;
+    const int *order;          // null: y is in tile order
     const int *cell;
     const float *frac;
     const int *toff;           // toff[ntiles] = end of finite points
@@ -242,7 +242,7 @@ struct KbnSpreadArgs {
     int64_t gsize;
     int nch;
     int64_t M;
-    const int *order;
+    const int *order;          // null: y is in tile order (then rec_q is rec_p)
     const int *cell;
     const float *frac;
     const int *toff;
@@ -252,7 +252,7 @@ struct KbnSpreadArgs {
     const int *scounts;        // [0] work items, [1] multi-item tiles
     float2 *partial;           // [smax][nch][prod To] partial tiles of multi-item tiles
     const int *rec_p;          // per owner-list entry: sorted sample position
-    const int *rec_q;          // per owner-list entry: the sample's index in the caller's order
+    const int *rec_q;          // per owner-list entry: the sample's index in y
     const int2 *rec_t;         // [entries][D] tap origin relative to the owning tile, window fraction (float bits)
     int nwork_max, ncomb_max;
 };

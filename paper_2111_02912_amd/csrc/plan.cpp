@@ -641,10 +641,12 @@ KbnGatherArgs t2_gather_args(kbn_plan p, int64_t nch, int ncc, int nw, int mode,
 // Forward-type pipeline: FFT passes, then gather.  mode 0 writes y; mode 1
 // folds the omega-Jacobian.  ext_ws (mode 0 only): a workspace of ext_bytes
 // given by the caller instead of the plan's, which is then neither grown
-// nor used; the batch is chunked to fit it.
+// nor used; the batch is chunked to fit it.  tile_order (mode 0 only): y is
+// written in tile order instead of the caller's.
 int run_type2(kbn_plan p, int B, int C, int nw, int weighted, const float2 *x,
               const float2 *smaps, int mode, float2 *y, const float2 *v, float *dom,
-              int accumulate, hipStream_t stream, void *ext_ws = nullptr, int64_t ext_bytes = 0) {
+              int accumulate, hipStream_t stream, void *ext_ws = nullptr, int64_t ext_bytes = 0,
+              bool tile_order = false) {
     const int64_t gsz = p->gsize();
     const int64_t per_coil = (int64_t)nw * gsz * (int64_t)sizeof(float2) * 2;
     const Chunks ck = split_chunks(B, C, per_coil, ext_ws ? ext_bytes : p->max_ws);
@@ -668,8 +670,9 @@ int run_type2(kbn_plan p, int B, int C, int nw, int weighted, const float2 *x,
         int rc = t2_passes(p, nw, weighted, x, smaps, b0, c0, nb, ncc, bufA, bufB, &grid, stream);
         if (rc == KBN_OK) rc = points_wait(p, stream, true);  // the FFT passes overlap the index pass
         if (rc != KBN_OK) return rc;
-        const KbnGatherArgs ga = t2_gather_args(p, nch, ncc, nw, mode, grid, (b0 * C + c0) * p->M, y, v, dom, part,
-                                                (accumulate || b0 > 0 || c0 > 0) ? 1 : 0);
+        KbnGatherArgs ga = t2_gather_args(p, nch, ncc, nw, mode, grid, (b0 * C + c0) * p->M, y, v, dom, part,
+                                          (accumulate || b0 > 0 || c0 > 0) ? 1 : 0);
+        if (tile_order) ga.order = nullptr;
         KBN_LAUNCH(mode == 0 ? KBN_CLASS_GATHER : KBN_CLASS_GATHER_JAC, kbn_launch_gather(geom, ga, mode, stream), "gather");
     }
     return KBN_OK;
@@ -765,9 +768,10 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
 
 // Adjoint pipeline: spread, inverse FFT passes with cropping, scaling and
 // conj(coil map) summed over coils.  With coil_images (see t1_passes) the sum
-// is left to the caller where the whole batch is one chunk.
+// is left to the caller where the whole batch is one chunk.  tile_order: y is
+// in tile order (run_type2), not in the caller's.
 int run_type1(kbn_plan p, int B, int C, const float2 *y, const float2 *smaps, float2 *x,
-              hipStream_t stream, const float2 **coil_images = nullptr) {
+              hipStream_t stream, const float2 **coil_images = nullptr, bool tile_order = false) {
     const int64_t gsz = p->gsize();
     const int64_t per_coil = type1_per_coil(p, p->M);
     const Chunks ck = split_chunks(B, C, per_coil, p->max_ws);
@@ -785,7 +789,11 @@ int run_type1(kbn_plan p, int B, int C, const float2 *y, const float2 *smaps, fl
         const int64_t nb = std::min<int64_t>(ck.bc, B - b0);
         const int ncc = std::min(ck.cc, C - c0);
         const int64_t nch = nb * ncc;
-        const KbnSpreadArgs sa = t1_spread_args(p, nch, y + (b0 * C + c0) * p->M, bufA, bufY, bufP);
+        KbnSpreadArgs sa = t1_spread_args(p, nch, y + (b0 * C + c0) * p->M, bufA, bufY, bufP);
+        if (tile_order) {
+            sa.order = nullptr;
+            sa.rec_q = sa.rec_p;
+        }
         KBN_LAUNCH(KBN_CLASS_SPREAD, kbn_launch_spread(geom, sa, stream), "spread");
         rc = t1_passes(p, b0, c0, nb, ncc, smaps, x, bufA, bufB, stream,
                        ck.bc == B && ck.cc == C ? coil_images : nullptr);
@@ -1559,14 +1567,19 @@ int kbn_cg_step(kbn_plan p, int B, int C, const void *smaps, double lambda, int 
     int64_t npix = 1;
     for (int d = 0; d < p->D; ++d) npix *= p->N[d];
     for (int it = 0; it < iters; ++it) {
-        // q = E^H E p for every image (+ lambda T^H T p in the vector kernel)
+        // q = E^H E p for every image (+ lambda T^H T p in the vector kernel).
+        // E p stays between the two calls, so it is kept in tile order: the
+        // gather's stores and the spread's loads are whole lines instead of 8
+        // bytes of a line each (uniform random samples, 256^2, 8 coils, M =
+        // 98304: gather 16 -> 13.5, spread 27 -> 22.5 us;
+        // ten iterations 990 -> 918 us)
         if (p->M > 0) {
             rc = run_type2(p, B, C, 1, 0, b.p, (const float2 *)smaps, 0, b.ytmp, nullptr, nullptr, 0,
-                           stream);
+                           stream, nullptr, 0, true);
             if (rc != KBN_OK) return rc;
         }
         const float2 *coils = nullptr;
-        rc = run_type1(p, B, C, b.ytmp, (const float2 *)smaps, b.q, stream, &coils);
+        rc = run_type1(p, B, C, b.ytmp, (const float2 *)smaps, b.q, stream, &coils, true);
         if (rc != KBN_OK) return rc;
         rc = cg_launch(p, KBN_CGK_Q, B, npix, (float2 *)x, b, (float)lambda, reg, stream, coils, C);
         if (rc == KBN_OK) rc = cg_launch(p, KBN_CGK_XR, B, npix, (float2 *)x, b, 0.f, reg, stream);

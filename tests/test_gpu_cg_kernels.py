@@ -65,3 +65,29 @@ def test_cg_iterations_match_fp64_vectors(N, M, B, C, reg, ws):
     print("  ", err.max().item(), flush=True)
     assert err.max().item() < TOL
     assert torch.allclose(rel.double().cpu().flatten(), res.cpu(), rtol=100 * TOL, atol=TOL)
+
+
+# E p in tile order through every spread kernel (matrix cores, output
+# stationary, scatter), with and without samples whose location is not finite
+@pytest.mark.parametrize("N,tile", [((40, 36), None), ((40, 36), 16), ((40, 36), 24), ((12, 14, 10), None),
+                                    ((12, 14, 10), 10), ((300,), None)])
+def test_cg_keeps_flagged_samples_out(N, tile):
+    from paper_2111_02912_amd.cg import cg_sense
+    from paper_2111_02912_amd.nufft import KbNufft
+    print(f"cg flagged N={N} spread_tile={tile}", flush=True)
+    dev = torch.device("cuda", 0)
+    M, C = 3000, 3
+    om = W.uniform_random(M, len(N), seed=53)
+    smaps = torch.from_numpy(W.sense_maps(C, N)).to(dev) if len(N) > 1 else None
+    y = W.complex_normal((1, C if len(N) > 1 else 1, M), 54)
+    bad = om.copy()
+    bad[::7, len(N) - 1] = np.nan
+    keep = np.arange(M) % 7 != 0
+    kw = {} if tile is None else {"spread_tile": tile}
+    out = []
+    for o, v in ((bad, y), (om[keep], np.ascontiguousarray(y[..., keep]))):
+        plan = KbNufft(N, device=dev, **kw)
+        plan.set_points(torch.from_numpy(o).to(dev))
+        out.append(cg_sense(plan, torch.from_numpy(v).to(dev), smaps, lam=float(M), iters=3)[0])
+    assert torch.isfinite(torch.view_as_real(out[0])).all()
+    assert torch.equal(out[0], out[1])
