@@ -243,7 +243,8 @@ int kbn_jac_omega_fwd(kbn_plan p, int B, int C, const void *x, const void *smaps
  * per image-coil pair than the two separate calls.  y equals kbn_forward's
  * bit for bit; domega agrees with kbn_jac_omega_fwd to float32 rounding
  * (the r^[0] scaling is applied after the first pass instead of before).
- * Other dimensions and FFT lengths run the two calls.  x: c64 [B][N...];
+ * Other dimensions, and grids with an edge below 128 (launch-bound), run
+ * the two calls.  x: c64 [B][N...];
  * y, g: c64 [B][C][M] (y and g must not overlap); domega: device float32
  * [M][D]; accumulate = 0 overwrites domega, 1 adds.  The workspace holds
  * D + 1 grids per image-coil pair (kbn_plan_footprint does not count it).
@@ -521,14 +522,16 @@ int kbn_batch_capture(kbn_batch b, void *stream);
  *      Jacobian expressions evaluated as extra NUFFTs of x weighted by the
  *      coordinate grids, folded with the upstream gradient), and one
  *      output-stationary spread launch for all ADJOINT / JAC_X_FWD tasks
- *      with the same owner-tile shape and channels per thread (the
- *      transpose of the interpolation, A(omega)^H y);
+ *      with the same 2D owner tiles of more than 8 cells per axis and the
+ *      same channels per thread (the transpose of the interpolation,
+ *      A(omega)^H y);
  *   3. each task's epilogue on its stream: the omega-gradient's sum over
  *      channel groups, or the adjoint's split-tile sums and inverse FFT
  *      passes.
  * A task that needs several workspace chunks, has no points, or whose
- * interpolation takes another kernel (an unstaged gather, the
- * channel-per-lane or scatter spread) runs whole in phase 1.  Results are
+ * interpolation takes another kernel (an unstaged gather, the matrix-core
+ * spread of the default owner tiles, the scatter spread) runs whole in
+ * phase 1.  Results are
  * bitwise those of the single calls.  Because the phases of different tasks
  * interleave, fused tasks must be independent even within one plan: no task
  * may read another task's output, and only JAC_OMEGA tasks with accumulate

@@ -798,8 +798,9 @@ k_spread_os_multi(const KbnSpreadJob *__restrict__ jobs, const int *__restrict__
 // channels (whose 0.54 GB of grid take 0.1 ms to write) 235 -> 194 us.
 // Measured and not kept: one autonomous wave per item without staging
 // (927 us at 96^3, the weights evaluated per slice), workgroups that stay
-// resident and load across items (744 us: static shares), batches sorted by
-// slice so that a wave could own all slices (693-920 us).
+// resident and load across items (744 us: static shares; in 2D 29 -> 26 us at
+// 384^2 x 8 coils, but 192 -> 201 us at 256 channels), batches sorted by slice
+// so that a wave could own all slices (693-920 us).
 typedef float mf_f4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ mf_f4 mfma4(float a, float b, mf_f4 c) {
@@ -982,12 +983,12 @@ k_permute_groups(const float2 *__restrict__ y, float2 *__restrict__ ys, const in
 
 // 3D: a workgroup of 8 / S * CS waves per (work item, 8 / S channels), each
 // wave taking S adjacent x-slices of the tile and, of their four 2-row blocks,
-// 4 / CS.  The 16 reals of A are the S slices x
-// 8 / S channels, A = w_x * y, and B = w_y * w_z over the 8 x 8 cells of a
-// slice, so that few channels still fill the operand.  Of each batch a wave
-// visits only the entries that reach its slices (a footprint covers 6 of the
-// 13 positions of its first tap around an 8-cell tile), through a list of
-// record offsets padded with the zero record.
+// 4 / CS.  The 16 reals of A are the S slices x 8 / S channels, A = w_x * y,
+// and B = w_y * w_z over the 8 x 8 cells of a slice, so that few channels still
+// fill the operand.  Of each batch a wave visits only the entries that reach
+// its slices (a footprint covers 6 of the 13 positions of its first tap around
+// an 8-cell tile), through a list of record offsets padded with the zero
+// record.
 template <int J, int S, int CS>
 __global__ void __launch_bounds__(512 / S * CS, S == 2 ? 5 : 6) k_spread_mf3(KbnGeom g, KbnSpreadArgs a) {
     constexpr int CG = 8 / S;             // channels per group

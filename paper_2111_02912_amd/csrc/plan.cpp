@@ -1220,8 +1220,8 @@ int index_pass(kbn_plan p, int64_t M, const float *omega, const KbnPointsBufs &b
     KBN_LAUNCH(KBN_CLASS_INDEX,
                kbn_launch_owner_lists(p->geom(), M, p->cell, p->frac, p->toff, p->order,
                                       p->counts + kbn_points_owner_base(M, p->ntiles), p->ooff, p->otile_order,
-                                      KBN_SPREAD_SEG, spread_slots(p, M), p->swork, p->scomb, p->scounts, p->rec_p, p->rec_q,
-                                      p->rec_t, stream),
+                                      KBN_SPREAD_SEG, spread_slots(p, M), p->swork, p->scomb, p->scounts, p->rec_p,
+                                      p->rec_q, p->rec_t, stream),
                "spread lists");
     return KBN_OK;
 }

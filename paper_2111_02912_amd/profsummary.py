@@ -52,20 +52,20 @@ def kernel_class(name: str):
     if any(base.startswith(k) for k in _INDEX):
         return "index"
     ta = _targs(name)
-    if base in ("k_first_pass", "k_rows_first"):
+    if base in ("k_first_pass", "k_rows_first", "k_any_first"):
         return "fft_first"
-    if base in ("k_last_adj", "k_rows_last_adj"):
+    if base in ("k_last_adj", "k_rows_last_adj", "k_any_last", "k_coil_sum"):
         return "fft_last_adj"
-    if base in ("k_cols", "k_cols_pf", "k_mid_pass"):
-        # k_cols[_pf]<L, E, INV, NT[, DER]>, k_mid_pass<MAXE, INV>
-        inv = ta[2] if base.startswith("k_cols") and len(ta) > 2 else (ta[1] if len(ta) > 1 else "false")
+    if base in ("k_cols", "k_cols_pf", "k_any_cols", "k_mid_pass"):
+        # k_cols[_pf]<L, E, INV, NT[, DER]>, k_any_cols<L, INV, HALF>, k_mid_pass<MAXE, INV>
+        inv = ta[2] if base in ("k_cols", "k_cols_pf") and len(ta) > 2 else (ta[1] if len(ta) > 1 else "false")
         return "fft_mid_inv" if inv == "true" else "fft_mid_fwd"
     if base in ("k_gather_staged", "k_gather"):
         # <D, J, MODE, ...>
         return "gather_jac" if len(ta) > 2 and ta[2] == "1" else "gather"
     if base == "k_reduce_parts":
         return "gather_jac"
-    if base.startswith("k_spread") or base == "k_permute":
+    if base.startswith("k_spread") or base.startswith("k_permute"):
         return "spread"
     return None
 
@@ -73,7 +73,7 @@ def kernel_class(name: str):
 # sources of the NUFFT kernels, their launch configuration and the plan
 # (the CG, off-resonance and batch sources do not affect those kernels)
 NUFFT_SOURCES = ("kbn_internal.h", "kbn_window.h", "plan.cpp", "points.hip", "fft.hip", "fft_fast.hip",
-                 "interp.hip")
+                 "fft_any.h", *(f"fft_any_{u}.hip" for u in range(6)), "interp.hip")
 
 
 def sources_hash() -> str:
