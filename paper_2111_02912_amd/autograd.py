@@ -52,9 +52,16 @@ class _ForwardOp(torch.autograd.Function):
         plan.ensure_points(omega)
         g = g.contiguous()
         gx = gom = None
+        # 3D: the omega-Jacobian first, which reads the sorted samples only, while
+        # the spread lists of a new trajectory are still being built (75 x 90 x 64
+        # training step 1.08 -> 1.01 ms).  In 2D they are done by now, and the
+        # adjoint first finds g in cache (320^2: 0.93 against 0.94 ms).
+        jac_first = plan.D == 3
+        if ctx.needs_input_grad[1] and jac_first:
+            gom = plan.jac_omega_fwd(x, g, smaps)
         if ctx.needs_input_grad[0]:
             gx = plan.jac_x(_lib.KBN_OP_FORWARD, g, smaps).reshape(ctx.xshape)
-        if ctx.needs_input_grad[1]:
+        if ctx.needs_input_grad[1] and not jac_first:
             gom = plan.jac_omega_fwd(x, g, smaps)
         return gx, gom, None, None
 
