@@ -126,6 +126,7 @@ __device__ void subproblems_block(int nbins, int sub, const int *__restrict__ to
 // Bins x chunks matrices up to this many counts are scanned by one workgroup
 // through LDS (48 KiB); larger ones by the three-phase scan below.
 #define KBN_SCAN_SMALL 12288
+#define KBN_SCAN_COUNTS ((int64_t)1 << 20)  // a larger matrix only where 4096 samples per chunk need it
 
 // One workgroup: exclusive scan of the S bin-major counts in place
 // (counts[b * nchunks + c] becomes the first output position of chunk c's
@@ -798,11 +799,17 @@ int kbn_points_chunks(int64_t M, int ntiles, int *chunk) {
     }
     // at most 4096 samples per chunk (one wavefront ranks a chunk in steps of
     // 64); otherwise as many chunks as keep the count matrix within one
-    // workgroup's scan, and at least 256 samples per chunk
+    // workgroup's scan, and at least 256 samples per chunk.  Where 4096 samples
+    // already take the multi-workgroup scan, smaller chunks cost it little and
+    // fill the GPU, until the strided counts of a million entries cost more
+    // (index pass of 48^3 with 65536 samples 330 -> 264 us, 75 x 90 x 64 with
+    // 150001 447 -> 391, of it histogram 35 -> 17 and scatter 72 -> 38; 262144
+    // entries 279 and 433 us; 96^3 with 1M samples has 13825 bins and stays).
     const int64_t nmin = (M + 4095) / 4096;
     const int64_t nsmall = std::max<int64_t>(1, KBN_SCAN_SMALL / nbins);
     const int64_t n256 = std::max<int64_t>(1, M / 256);
-    const int64_t want = std::max(nmin, std::min(nsmall, n256));
+    const int64_t want = nmin <= nsmall ? std::max(nmin, std::min(nsmall, n256))
+                                        : std::max(nmin, std::min(n256, KBN_SCAN_COUNTS / nbins));
     int64_t c = (M + want - 1) / want;
     c = (c + 63) / 64 * 64;
     *chunk = (int)c;

@@ -2,9 +2,11 @@
 running beside them: the gathers start after its sort, the spreads after its
 owner lists.  Every result has the bits of the same call on a plan whose pass
 is known to have ended."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import points_ref
 from paper_2111_02912_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -45,3 +47,25 @@ def test_calls_behind_set_points(N, Ms, other_stream):
     torch.cuda.synchronize()
     for g, w in zip(got, want):
         assert all(torch.equal(a, b) for a, b in zip(g, w))
+
+
+# sizes on both sides of the rules for the samples per histogram chunk (the
+# one-workgroup scan, the larger scan at 256 samples and more per chunk, the
+# larger scan at its limit of counts), with samples whose location is not finite
+@pytest.mark.parametrize("N,M", [((48, 48, 48), 28672), ((48, 48, 48), 28673), ((48, 48, 48), 65536),
+                                 ((75, 90, 64), 150001), ((30, 30, 30), 150000), ((256, 250), 300001)])
+def test_sorted_order_for_every_chunking(N, M):
+    from paper_2111_02912_amd.nufft import KbNufft
+    print(f"sorted order N={N} M={M}", flush=True)
+    om = W.uniform_random(M, len(N), seed=81)
+    om[5::1000, 0] = np.inf
+    p = KbNufft(N, device=torch.device("cuda", 0))
+    p.set_points(torch.from_numpy(om).to(p.device))
+    got = {k: v.cpu().numpy() for k, v in p.get_points().items()}
+    cell, frac, bad = points_ref.cells(om, p.K)
+    tid, nt = points_ref.tiles(cell, p.K, p.tile, bad)
+    perm, off = points_ref.tile_order(tid, nt)
+    assert np.array_equal(got["order"], perm)
+    assert np.array_equal(got["offsets"], off)
+    assert np.array_equal(got["cell"], cell[perm].T)
+    assert np.array_equal(got["frac"].view(np.uint32), frac[perm].T.copy().view(np.uint32))
