@@ -415,6 +415,18 @@ int points_wait(kbn_plan p, hipStream_t stream, bool sorted_only) {
     if (sorted_only && p->sorted_gen == p->points_gen && p->sorted_stream == stream) return KBN_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cs) != hipSuccess) return fail(KBN_ERR_HIP, "hipStreamIsCapturing");
+    if (cs != hipStreamCaptureStatusNone && p->sorted_gen == p->points_gen && p->sorted_stream == stream) {
+        // a gather of this stream ran behind the sort of this pass before the
+        // capture: wait for the lists, which are being built or done, on the host
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess)
+            return fail(KBN_ERR_HIP, "hipThreadExchangeStreamCaptureMode");
+        const hipError_t e = hipEventSynchronize(p->points_ready);
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess || e != hipSuccess)
+            return fail(KBN_ERR_HIP, "hipEventSynchronize (points, under capture)");
+        p->points_pending = false;
+        return KBN_OK;
+    }
     if (cs != hipStreamCaptureStatusNone)  // (no event query either: not allowed in every capture mode)
         return fail(KBN_ERR_UNSUPPORTED,
                     "capture while the index pass of kbn_set_points may still run: call kbn_check_error first");

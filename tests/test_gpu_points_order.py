@@ -69,3 +69,35 @@ def test_sorted_order_for_every_chunking(N, M):
     assert np.array_equal(got["offsets"], off)
     assert np.array_equal(got["cell"], cell[perm].T)
     assert np.array_equal(got["frac"].view(np.uint32), frac[perm].T.copy().view(np.uint32))
+
+
+def test_capture_of_an_adjoint_behind_an_eager_forward():
+    """A stream whose forward call already waited for the points may capture
+    an adjoint on them; the replays give the eager call's bits."""
+    from paper_2111_02912_amd.nufft import KbNufft
+    print("capture behind an eager forward", flush=True)
+    dev = torch.device("cuda", 0)
+    N, M = (24, 30, 20), 40000
+    plan = KbNufft(N, device=dev)
+    om = torch.from_numpy(W.uniform_random(M, 3, seed=91)).to(dev)
+    x = torch.from_numpy(W.complex_normal((1,) + N, 92)).to(dev)
+    y = torch.from_numpy(W.complex_normal((1, 1, M), 93)).to(dev)
+    plan.set_points(om)
+    plan.check_error()
+    want = plan.adjoint(y).clone()  # (and the workspace at its size)
+    s = torch.cuda.Stream(dev)
+    s.wait_stream(torch.cuda.current_stream(dev))
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        plan.set_points(om)
+        plan.forward(x)
+        g.capture_begin()
+        out = plan.adjoint(y)
+        g.capture_end()
+    for _ in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        out.zero_()
+        plan.forward(x)
+        torch.cuda.synchronize()
