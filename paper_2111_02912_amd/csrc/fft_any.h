@@ -507,12 +507,13 @@ hipError_t any_first(const KbnFirstPassArgs &a, const float2 *tw, hipStream_t s)
 template <int L, bool INV, bool HALF>
 hipError_t any_cols(const KbnMidPassArgs &a, const float2 *tw, int64_t total, hipStream_t s) {
     constexpr size_t LDS = sizeof(float2) * L * col_lines(L);
+    constexpr int NT = col_threads(L);  // (evaluated per launch if it is not a constant here: 2 - 3 us)
     if constexpr (LDS > 64 * 1024) {  // opt in to more than the default (once)
         static const hipError_t ok = hipFuncSetAttribute(
             (const void *)k_any_cols<L, INV, HALF>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS);
         if (ok != hipSuccess) return ok;
     }
-    k_any_cols<L, INV, HALF><<<dim3((unsigned)total), dim3(col_threads(L)), LDS, s>>>(a, tw);
+    k_any_cols<L, INV, HALF><<<dim3((unsigned)total), dim3(NT), LDS, s>>>(a, tw);
     return hipGetLastError();
 }
 
