@@ -295,25 +295,10 @@ __device__ __forceinline__ void gather_staged_wg(const KbnGeom &g, const KbnGath
     }
 }
 
-// Workgroup x -> subproblem: consecutive workgroups go to the 8 XCDs in turn,
-// so runs of KBN_XCD_RUN consecutive subproblems are dealt to one XCD at a
-// time; the regions of a split tile and of neighbouring tiles then meet in
-// one L2 while the runs stay short enough to balance the XCDs (96^3 x 8
-// channels: 2.6 -> 1.2 GB fetched, 434 -> 402 us; 256^2 x 256: 1.17 -> 0.67 GB,
-// 195 -> 186 us; runs of 4 the same, of 32 and whole-XCD ranges slower).
-#define KBN_XCD_RUN 8
-__host__ __device__ inline int64_t xcd_padded(int64_t n) {
-    return (n + 8 * KBN_XCD_RUN - 1) / (8 * KBN_XCD_RUN) * (8 * KBN_XCD_RUN);
-}
-__device__ __forceinline__ int xcd_run_index(int x) {
-    const int q = x >> 3;
-    return ((q / KBN_XCD_RUN) * 8 + (x & 7)) * KBN_XCD_RUN + q % KBN_XCD_RUN;
-}
-
 template <int D, int J, int MODE, int CP, int MAXC>
 __global__ void __launch_bounds__(KBN_BLOCK) k_gather_staged(KbnGeom g, KbnGatherArgs a, int cg) {
     extern __shared__ float4 reg4[];
-    gather_staged_wg<D, J, MODE, CP, MAXC>(g, a, cg, xcd_run_index(blockIdx.x), blockIdx.y, reg4);
+    gather_staged_wg<D, J, MODE, CP, MAXC>(g, a, cg, kbn_xcd_run_index(blockIdx.x, gridDim.x), blockIdx.y, reg4);
 }
 
 // The staged gathers of several plans in one launch: workgroup w belongs to
@@ -1287,7 +1272,7 @@ hipError_t gather_dj(const KbnGeom &g, const KbnGatherArgs &a, int mode, hipStre
     const KbnGatherShape sh = kbn_gather_shape(g, a.M, a.nch, a.nw);
     dim3 grid((unsigned)sh.blocks, (unsigned)sh.groups);
     if (sh.staged) {
-        grid.x = (unsigned)xcd_padded(sh.blocks);
+        grid.x = (unsigned)kbn_xcd_padded(sh.blocks);
         // region cells per thread, loaded ahead in registers: the default
         // tiles' 37^2 (6) and 13^3 (9, or 10 with an edge of 9), in 3D up to
         // the 12 of 48 KiB.  Measured in 2D against loading them between the
