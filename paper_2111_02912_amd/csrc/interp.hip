@@ -1250,7 +1250,10 @@ KbnGatherShape kbn_gather_shape(const KbnGeom &g, int64_t M, int nch, int nw) {
     sh.blocks = blocks;
     const int64_t groups = kbn_gather_groups(blocks, nbc);
     sh.cg = (int)(((nbc + groups - 1) / groups) * nw);
-    if (nw == 1) sh.cg += sh.cg & 1;  // whole channel pairs: 8 channels one by one 21 us, in pairs 16 us
+    // the staged gather's whole channel pairs (8 channels one by one 21 us, in
+    // pairs 16 us); the direct one takes a channel at a time (40 x 48 x 36 x 2,
+    // J = 8: a workgroup row per channel 117 us, one for both 171)
+    if (nw == 1 && sh.staged) sh.cg += sh.cg & 1;
     sh.groups = (nch + sh.cg - 1) / sh.cg;
     return sh;
 }

@@ -19,6 +19,20 @@ int main(int, char **v) {
         std::printf("%lld", (long long)p);
         for (int x = 0; x < p; ++x) std::printf(" %d", kbn_xcd_run_index(x, (int)p));
     }
+    if (!std::strcmp(v[1], "gather")) {  // D J M channels weights K.. T..: staged, blocks, channels per group, groups
+        KbnGeom g = {};
+        g.D = std::atoi(v[2]);
+        g.J = std::atoi(v[3]);
+        g.ntiles = 1;
+        for (int d = 0; d < g.D; ++d) {
+            g.K[d] = std::atoi(v[7 + d]);
+            g.T[d] = std::atoi(v[7 + g.D + d]);
+            g.nt[d] = (g.K[d] + g.T[d] - 1) / g.T[d];
+            g.ntiles *= g.nt[d];
+        }
+        const KbnGatherShape sh = kbn_gather_shape(g, std::atoll(v[4]), std::atoi(v[5]), std::atoi(v[6]));
+        std::printf("%d %d %d %d", (int)sh.staged, (int)sh.blocks, sh.cg, sh.groups);
+    }
     std::printf("\n");
 }
 """
@@ -45,6 +59,14 @@ def test_gather_rows_hold_every_subproblem_once(rules, n):
     padded, *index = rules("xcd", n)
     assert padded % 8 == 0 and n <= padded < n + 8
     assert sorted(index) == list(range(padded))
+
+
+@pytest.mark.parametrize("nch", [1, 2, 3, 7, 24])
+def test_direct_gather_takes_channels_one_by_one(rules, nch):
+    """Few point blocks without an LDS region: a workgroup row per channel."""
+    staged, blocks, cg, groups = rules("gather", 3, 8, 40000, nch, 1, 80, 96, 72, 8, 8, 8)
+    assert not staged and blocks * nch < 8192
+    assert cg == 1 and groups == nch
 
 
 def test_launches_compute_no_splits():
