@@ -1219,13 +1219,22 @@ k_reduce_parts(float *__restrict__ dst, const float *__restrict__ part, int64_t 
 
 }  // namespace
 
-// About KBN_GATHER_WG_TARGET workgroups over point blocks x groups: five are
-// resident per CU, and their durations differ with the points they hold, so
-// several rounds of them even out (256^2 x 256 channels, forward and
-// omega-Jacobian: 2048 177 and 285 us, 4096 161 and 262, 8192 157 and 249, more
-// the same; fewer than 2048 is slower from 64 channels on).
+// Channel groups of a gather over `blocks` point blocks and nbc image-coil
+// pairs.  At least the KBN_GATHER_WG_MIN workgroups that fill the GPU; beyond
+// that KBN_GATHER_WG_TARGET of them, whose durations differ with the points they
+// hold, so that several rounds even out (five are resident per CU), but only
+// while a group keeps KBN_GATHER_PAIRS pairs: every group repeats the points'
+// weights, and an omega-Jacobian writes and sums one partial gradient per group.
+// Forward and omega-Jacobian of 256^2 x 256 channels: target 2048 177 and 285 us,
+// 4096 161 and 262, 8192 157 and 249, more the same.  The target without the
+// bound on pairs against with it, whole omega-Jacobian calls: 48^2 x 400 121 and 99
+// us, 64^2 x 64 56 and 48, 192^2 x 32 94 and 85, 256^2 x 2 with M = 2M 154 and 127,
+// 75 x 90 x 64 x 4 534 and 515; forward 180 and 166 there, but 27 x 27 x 35 x 24
+// (sigma 1.25) 85 and 92 (two pairs kept 85, and 40^3 x 32 then 193 instead of 187).
 int64_t kbn_gather_groups(int64_t blocks, int64_t nbc) {
-    return std::max<int64_t>(1, std::min<int64_t>(nbc, (KBN_GATHER_WG_TARGET + blocks - 1) / blocks));
+    const int64_t fill = (KBN_GATHER_WG_MIN + blocks - 1) / blocks;
+    const int64_t even = std::min((KBN_GATHER_WG_TARGET + blocks - 1) / blocks, nbc / KBN_GATHER_PAIRS);
+    return std::max<int64_t>(1, std::min<int64_t>(nbc, std::max(fill, even)));
 }
 
 // Launch shape of the gather: staged (LDS region fits 48 KiB) or direct, and

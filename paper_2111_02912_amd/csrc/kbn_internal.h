@@ -18,7 +18,9 @@
 #define KBN_BLOCK 256
 #define KBN_INDEX_STREAM_MIN 8192  // points from which the index pass runs beside the caller's stream
 #define KBN_SUB 256        // sorted points per gather subproblem (one per thread)
-#define KBN_GATHER_WG_TARGET 8192  // workgroups a gather aims for (point blocks x channel groups)
+#define KBN_GATHER_WG_MIN 2048     // workgroups (point blocks x channel groups) that fill the GPU
+#define KBN_GATHER_WG_TARGET 8192  // workgroups a gather aims for while its groups keep
+#define KBN_GATHER_PAIRS 4         // this many image-coil pairs
 #define KBN_SPREAD_EB 64   // list entries staged per spread batch
 #define KBN_SPREAD_SEG 128  // list entries per spread work item (doubled if slots run out)
 #define KBN_SPREAD_SMAX 256 // partial-tile slots for tiles split into several work items

@@ -69,6 +69,22 @@ def test_direct_gather_takes_channels_one_by_one(rules, nch):
     assert cg == 1 and groups == nch
 
 
+# (M, image-coil pairs, weights, K, T): one wave of subproblems and many, few
+# pairs and many
+@pytest.mark.parametrize("M,nbc,nw,K,T", [
+    (2000000, 2, 2, (512, 512), (32, 32)), (8192, 64, 2, (128, 128), (32, 32)), (3000, 400, 2, (96, 96), (32, 32)),
+    (30000, 8, 2, (384, 384), (16, 16)), (32768, 256, 1, (512, 512), (32, 32)), (150000, 4, 3, (150, 180, 128), (8, 8, 8)),
+    (20480, 64, 1, (400, 400), (32, 32)), (3000, 200, 1, (400,), (256,)),
+])
+def test_gather_groups_keep_pairs_once_the_gpu_is_filled(rules, M, nbc, nw, K, T):
+    staged, blocks, cg, groups = rules("gather", len(K), 6, M, nbc * nw, nw, *K, *T)
+    assert cg % nw == 0 and (groups - 1) * cg < nbc * nw <= groups * cg
+    fill = -(-2048 // blocks)  # groups that fill the GPU
+    assert groups <= fill or cg // nw >= 4
+    if nbc >= 4 * 32:  # many pairs: several rounds of workgroups
+        assert blocks * groups >= min(8192, blocks * nbc // 8)
+
+
 def test_launches_compute_no_splits():
     """The column passes' thread counts are constants of their kernels, not
     searched for again at every launch."""
