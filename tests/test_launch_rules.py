@@ -61,11 +61,11 @@ def test_gather_rows_hold_every_subproblem_once(rules, n):
     assert sorted(index) == list(range(padded))
 
 
-@pytest.mark.parametrize("nch", [1, 2, 3, 7, 24])
+@pytest.mark.parametrize("nch", [1, 2, 3, 7, 13])
 def test_direct_gather_takes_channels_one_by_one(rules, nch):
     """Few point blocks without an LDS region: a workgroup row per channel."""
     staged, blocks, cg, groups = rules("gather", 3, 8, 40000, nch, 1, 80, 96, 72, 8, 8, 8)
-    assert not staged and blocks * nch < 8192
+    assert not staged and blocks * nch < 2048 + blocks  # not more than fill the GPU
     assert cg == 1 and groups == nch
 
 
