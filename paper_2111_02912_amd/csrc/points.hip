@@ -594,7 +594,11 @@ k_owner_write(OwnerGeom o, int64_t M, const int *__restrict__ cell, const float 
                   });
 }
 
-__device__ __forceinline__ int owner_key(int c) { return c == 0 ? 32 : __clz(c); }  // larger counts first
+// Order of the tiles: bins (2^k, 2^(k+1)] of their entry count, larger first, so
+// that a bin holds either split tiles or unsplit ones (the entries per work item
+// are a power of two).
+#define KBN_OWN_KEYS 34
+__device__ __forceinline__ int owner_key(int c) { return c == 0 ? 33 : (c == 1 ? 32 : __clz(c - 1)); }
 
 // atomicAdd(&ctr[key], 1) for the active lanes of a wavefront, one LDS
 // atomic per distinct key (lanes with equal keys get consecutive values in
@@ -644,9 +648,10 @@ __device__ __forceinline__ void block_scan3_1024(int x[3], int ex[3], int tot[3]
     lds_barrier();
 }
 
-// One workgroup: owner offsets (exclusive scan of the counts, ooff[n] =
-// total), the tiles in decreasing order of entry count, and the spread work
-// items.
+// Owner offsets (exclusive scan of the counts, ooff[n] = total), the tiles in
+// decreasing order of entry count, and the spread work items; up to KBN_OWN_LDS
+// tiles in one workgroup, whose counts, offsets and order live in LDS (3 ntiles
+// ints) and are written out at the end.
 //
 // Order: bins of log2 count, so the spread dispatches its longest
 // workgroups first.  The order inside a bin is arbitrary; tiles are
@@ -659,28 +664,21 @@ __device__ __forceinline__ void block_scan3_1024(int x[3], int ex[3], int tot[3]
 // doubles until the slots fit in `smax`.  Outputs:
 //   work[i] = (tile, first entry, end entry, slot or -1), counts2[0] = items
 //   comb[k] = (tile, first slot, number of slots),     counts2[1] = tiles
-template <bool STAGED>
 __global__ void __launch_bounds__(1024)
 k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, int *__restrict__ ooff,
                int *__restrict__ order, int *__restrict__ work, int *__restrict__ comb,
                int *__restrict__ counts2) {
-    // STAGED: counts, offsets and order live in LDS (dynamic, 3 ntiles ints)
-    // and are written out at the end; else they are read and written in
-    // global memory
     extern __shared__ int lds[];
     __shared__ int wsum[16];
     __shared__ int wsum3[3][16];
-    __shared__ int hist[33], start[33];
+    __shared__ int hist[KBN_OWN_KEYS], start[KBN_OWN_KEYS];
     const int tid = threadIdx.x;
     const int nr = (ntiles + 1023) / 1024;
-    int *off = STAGED ? lds + ntiles : ooff;
-    int *ord = STAGED ? lds + 2 * ntiles : order;
-    if (STAGED) {
+    int *off = lds + ntiles, *ord = lds + 2 * ntiles;
 #pragma unroll 4
-        for (int t = tid; t < ntiles; t += 1024) lds[t] = ocount[t];
-        lds_barrier();
-    }
-    const int *cnt = STAGED ? lds : ocount;
+    for (int t = tid; t < ntiles; t += 1024) lds[t] = ocount[t];
+    lds_barrier();
+    const int *cnt = lds;
     // offsets
     int carry = 0;
     for (int r = 0; r < nr; ++r) {
@@ -692,7 +690,7 @@ k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, in
     }
     if (tid == 0) ooff[ntiles] = carry;
     // hottest-first order
-    if (tid < 33) hist[tid] = 0;
+    if (tid < KBN_OWN_KEYS) hist[tid] = 0;
     lds_barrier();
     for (int t0 = 0; t0 < ntiles; t0 += 1024) {
         const int t = t0 + tid;
@@ -701,7 +699,7 @@ k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, in
     lds_barrier();
     if (tid == 0) {
         int acc = 0;
-        for (int k = 0; k < 33; ++k) {
+        for (int k = 0; k < KBN_OWN_KEYS; ++k) {
             start[k] = acc;
             acc += hist[k];
         }
@@ -725,10 +723,7 @@ k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, in
         if (total <= smax) break;
         sg *= 2;
     }
-    if (STAGED)
-        lds_barrier();
-    else
-        __syncthreads();  // order and offsets complete in global memory
+    lds_barrier();
     // positions in rounds: prefixes of items, slots and split tiles, and the
     // position's items written at once
     int cw = 0, cs = 0, cc = 0;
@@ -765,12 +760,147 @@ k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, in
         counts2[0] = cw;
         counts2[1] = cc;
     }
-    if (STAGED) {
 #pragma unroll 4
-        for (int t = tid; t < ntiles; t += 1024) {
-            ooff[t] = off[t];
-            order[t] = ord[t];
+    for (int t = tid; t < ntiles; t += 1024) {
+        ooff[t] = off[t];
+        order[t] = ord[t];
+    }
+}
+
+// The same for more tiles, in spans of KBN_FIN_SPAN tiles: sums per span, one
+// workgroup that turns them into starting positions, and the spans again with
+// those.  The split tiles come first in the order (owner_key), so an unsplit
+// tile's item follows from its position, and the few split ones (at most half of
+// the partial slots) take their slots, items and combine entries from counters,
+// in any order.  One workgroup over all tiles took a round trip to memory per
+// thousand of them and phase: 105 us at 13824 tiles, 490 at 110592, 1130 at 262144.
+#define KBN_FIN_SPAN 4096
+#define KBN_FIN_LEVELS 24  // entries per work item: seg 2^level, up to 2^30
+struct FinScratch {        // [nb] or [keys][nb], [levels][nb]
+    int *head;             // log2 of the entries per item, split tiles, their slots, two counters
+    int *sum, *hist, *slots;
+};
+__host__ __device__ inline int fin_spans(int ntiles) { return (ntiles + KBN_FIN_SPAN - 1) / KBN_FIN_SPAN; }
+__host__ __device__ inline FinScratch fin_scratch(int *p, int nb) {
+    return FinScratch{p, p + 8, p + 8 + nb, p + 8 + nb * (1 + KBN_OWN_KEYS)};
+}
+inline int64_t fin_ints(int ntiles) {
+    return ntiles <= KBN_OWN_LDS ? 0 : 8 + (int64_t)fin_spans(ntiles) * (1 + KBN_OWN_KEYS + KBN_FIN_LEVELS);
+}
+
+__global__ void __launch_bounds__(1024)
+k_owner_spans(int ntiles, int nb, int seg_log, const int *__restrict__ ocount, int *__restrict__ scratch) {
+    __shared__ int wsum[16], hist[KBN_OWN_KEYS], slots[KBN_FIN_LEVELS];
+    const int tid = threadIdx.x;
+    const FinScratch f = fin_scratch(scratch, nb);
+    if (tid < KBN_OWN_KEYS) hist[tid] = 0;
+    if (tid < KBN_FIN_LEVELS) slots[tid] = 0;
+    int c[KBN_FIN_SPAN / 1024], sum = 0;
+#pragma unroll
+    for (int u = 0; u < KBN_FIN_SPAN / 1024; ++u) {
+        const int t = (int)blockIdx.x * KBN_FIN_SPAN + u * 1024 + tid;
+        c[u] = t < ntiles ? ocount[t] : -1;
+        sum += max(c[u], 0);
+    }
+    int total;
+    (void)block_scan_1024(sum, wsum, total);  // (its barriers order the cleared LDS too)
+#pragma unroll
+    for (int u = 0; u < KBN_FIN_SPAN / 1024; ++u) {
+        (void)wave_key_add(hist, c[u] >= 0 ? owner_key(c[u]) : 0, c[u] >= 0);
+        for (int l = 0; l < KBN_FIN_LEVELS && c[u] > 0 && ((c[u] - 1) >> (seg_log + l)) > 0; ++l)
+            atomicAdd(&slots[l], ((c[u] - 1) >> (seg_log + l)) + 1);
+    }
+    lds_barrier();
+    if (tid == 0) f.sum[blockIdx.x] = total;
+    if (tid < KBN_OWN_KEYS) f.hist[tid * nb + blockIdx.x] = hist[tid];
+    if (tid < KBN_FIN_LEVELS) f.slots[tid * nb + blockIdx.x] = slots[tid];
+}
+
+__global__ void __launch_bounds__(1024)
+k_owner_top(int ntiles, int nb, int seg_log, int smax, int *__restrict__ scratch, int *__restrict__ ooff,
+            int *__restrict__ counts2) {
+    __shared__ int wsum[16], lslots[KBN_FIN_LEVELS];
+    const int tid = threadIdx.x;
+    const FinScratch f = fin_scratch(scratch, nb);
+    int run = 0, tot;
+    for (int b0 = 0; b0 < nb; b0 += 1024) {
+        const int v = b0 + tid < nb ? f.sum[b0 + tid] : 0;
+        const int ex = block_scan_1024(v, wsum, tot);
+        if (b0 + tid < nb) f.sum[b0 + tid] = run + ex;
+        run += tot;
+    }
+    if (tid == 0) ooff[ntiles] = run;
+    for (int l = tid >> 6; l < KBN_FIN_LEVELS; l += 16) {  // one wavefront per level
+        int s = 0;
+        for (int b = tid & 63; b < nb; b += 64) s += f.slots[l * nb + b];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if ((tid & 63) == 0) lslots[l] = s;
+    }
+    lds_barrier();
+    int level = 0;
+    while (level < KBN_FIN_LEVELS - 1 && lslots[level] > smax) ++level;
+    const int first = __clz(1 << (seg_log + level)) + 1;  // the first key of unsplit tiles
+    run = 0;
+    for (int i0 = 0; i0 < KBN_OWN_KEYS * nb; i0 += 1024) {
+        const int i = i0 + tid;
+        const int v = i < KBN_OWN_KEYS * nb ? f.hist[i] : 0;
+        const int ex = block_scan_1024(v, wsum, tot);
+        if (i < KBN_OWN_KEYS * nb) f.hist[i] = run + ex;
+        if (i == first * nb) {
+            const int split = run + ex;
+            f.head[0] = seg_log + level;
+            f.head[1] = split;
+            f.head[2] = lslots[level];
+            f.head[3] = 0;
+            f.head[4] = 0;
+            counts2[0] = lslots[level] + ntiles - split;
+            counts2[1] = split;
         }
+        run += tot;
+    }
+}
+
+__global__ void __launch_bounds__(1024)
+k_owner_place(int ntiles, int nb, const int *__restrict__ ocount, int *__restrict__ scratch, int *__restrict__ ooff,
+              int *__restrict__ order, int *__restrict__ work, int *__restrict__ comb) {
+    __shared__ int wsum[16], start[KBN_OWN_KEYS];
+    const int tid = threadIdx.x;
+    const FinScratch f = fin_scratch(scratch, nb);
+    if (tid < KBN_OWN_KEYS) start[tid] = f.hist[tid * nb + blockIdx.x];
+    const int seg_log = f.head[0], split = f.head[1], slots = f.head[2];
+    int run = f.sum[blockIdx.x];
+#pragma unroll
+    for (int u = 0; u < KBN_FIN_SPAN / 1024; ++u) {
+        const int t = (int)blockIdx.x * KBN_FIN_SPAN + u * 1024 + tid;
+        const bool in = t < ntiles;
+        const int c = in ? ocount[t] : 0;
+        int tot;
+        const int e0 = run + block_scan_1024(c, wsum, tot);
+        run += tot;
+        const int q = wave_key_add(start, owner_key(c), in);
+        if (!in) continue;
+        ooff[t] = e0;
+        order[q] = t;
+        const int ns = c > 0 ? ((c - 1) >> seg_log) + 1 : 1;
+        if (ns == 1) {
+            int *w = work + 4 * ((int64_t)slots + q - split);
+            w[0] = t;
+            w[1] = e0;
+            w[2] = e0 + c;
+            w[3] = -1;
+            continue;
+        }
+        const int si = atomicAdd(&f.head[3], ns), k = atomicAdd(&f.head[4], 1);
+        for (int j = 0; j < ns; ++j) {
+            int *w = work + 4 * (si + j);
+            w[0] = t;
+            w[1] = e0 + (j << seg_log);
+            w[2] = j + 1 < ns ? e0 + ((j + 1) << seg_log) : e0 + c;
+            w[3] = si + j;
+        }
+        comb[3 * k] = t;
+        comb[3 * k + 1] = si;
+        comb[3 * k + 2] = ns;
     }
 }
 
@@ -783,7 +913,7 @@ hipError_t allow_large_lds(size_t bytes) {
     static const hipError_t once = [] {
         const void *ks[] = {(const void *)k_points_hist, (const void *)k_tile_scatter<1>,
                             (const void *)k_tile_scatter<2>, (const void *)k_tile_scatter<3>,
-                            (const void *)k_owner_finish<true>};
+                            (const void *)k_owner_finish};
         hipError_t r = hipSuccess;
         for (const void *k : ks) {
             // the dynamic part may take what the kernel's static LDS leaves
@@ -832,8 +962,8 @@ int64_t kbn_points_owner_base(int64_t M, int ntiles) {
 }
 
 int64_t kbn_points_counts_size(int64_t M, int ntiles, int ntiles_own) {
-    // then the owner tiles' entry counts
-    return kbn_points_owner_base(M, ntiles) + (int64_t)ntiles_own + 1;
+    // then the owner tiles' entry counts and the spans of k_owner_spans
+    return kbn_points_owner_base(M, ntiles) + (int64_t)ntiles_own + 1 + fin_ints(ntiles_own);
 }
 
 hipError_t kbn_launch_points(int D, int64_t M, const float *omega, const double *scale,
@@ -901,6 +1031,8 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
         o.nt[d] = d < g.D ? g.nt[d] : 1;
     }
     const int n = g.ntiles_own;
+    int seg_log = 0;
+    while ((1 << seg_log) < seg) ++seg_log;  // seg is a power of two
     {
         const hipError_t e = allow_large_lds(3 * sizeof(int) * (size_t)std::min(n, KBN_OWN_LDS));
         if (e != hipSuccess) return e;
@@ -911,12 +1043,17 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
         if (M > 0)                                                                                     \
             k_owner_count<d><<<dim3((unsigned)((M + KBN_BLOCK - 1) / KBN_BLOCK)), dim3(KBN_BLOCK), 0,  \
                                s>>>(o, M, cell, frac, toff, ocount);                                   \
-        if (n <= KBN_OWN_LDS)                                                                          \
-            k_owner_finish<true><<<dim3(1), dim3(1024), 3 * sizeof(int) * n, s>>>(                     \
+        if (n <= KBN_OWN_LDS) {                                                                        \
+            k_owner_finish<<<dim3(1), dim3(1024), 3 * sizeof(int) * n, s>>>(                           \
                 n, seg, smax, ocount, ooff, otile_order, swork, scomb, scounts);                       \
-        else                                                                                           \
-            k_owner_finish<false><<<dim3(1), dim3(1024), 0, s>>>(n, seg, smax, ocount, ooff,           \
-                                                                 otile_order, swork, scomb, scounts);  \
+        } else {                                                                                       \
+            const int nb = fin_spans(n);                                                               \
+            int *scratch = ocount + n + 1;                                                             \
+            k_owner_spans<<<dim3(nb), dim3(1024), 0, s>>>(n, nb, seg_log, ocount, scratch);            \
+            k_owner_top<<<dim3(1), dim3(1024), 0, s>>>(n, nb, seg_log, smax, scratch, ooff, scounts);  \
+            k_owner_place<<<dim3(nb), dim3(1024), 0, s>>>(n, nb, ocount, scratch, ooff, otile_order,   \
+                                                          swork, scomb);                               \
+        }                                                                                              \
         k_owner_write<d><<<dim3(n), dim3(KBN_OWN_BLOCK), 0, s>>>(o, M, cell, frac, toff, order, ooff,  \
                                                                  otile_order, rec_p, rec_q, rec_t);    \
         break;
