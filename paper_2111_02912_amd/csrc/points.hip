@@ -408,30 +408,40 @@ __device__ __forceinline__ bool owner_touch(const OwnerGeom &o, int p, int64_t M
     return hit;
 }
 
-// Wavefront 0 stages up to KBN_OWN_MAXC candidate sort tiles: their first
+// Threads that walk one owner tile's candidates: a workgroup of four
+// wavefronts (W = 4), or one wavefront (W = 1), whose LDS accesses complete in
+// program order.
+template <int W>
+__device__ __forceinline__ void walk_sync() {
+    if constexpr (W == 1) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        lds_barrier();
+    }
+}
+
+// The first wavefront stages up to KBN_OWN_MAXC candidate sort tiles: their first
 // sorted position and the exclusive prefix of their sizes (coff[nk] = total).
 template <int D>
 __device__ __forceinline__ void owner_stage(const OwnerGeom &o, const int first[3], const int num[3], int k0,
-                                            int nk, const int *__restrict__ toff, int *cbeg, int *coff) {
-    if (threadIdx.x < 64) {
-        const int k = threadIdx.x;
-        int b = 0, n = 0;
-        if (k < nk) {
-            const int st = owner_candidate<D>(o, first, num, k0 + k);
-            b = toff[st];
-            n = toff[st + 1] - b;
-        }
-        int inc = n;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int y = __shfl_up(inc, off, 64);
-            if (k >= off) inc += y;
-        }
-        if (k < nk) {
-            cbeg[k] = b;
-            coff[k] = inc - n;
-        }
-        if (k == nk - 1) coff[nk] = inc;
+                                            int nk, const int *__restrict__ toff, int *cbeg, int *coff, int k) {
+    int b = 0, n = 0;
+    if (k < nk) {
+        const int st = owner_candidate<D>(o, first, num, k0 + k);
+        b = toff[st];
+        n = toff[st + 1] - b;
     }
+    int inc = n;
+    for (int off = 1; off < 64; off <<= 1) {
+        const int y = __shfl_up(inc, off, 64);
+        if (k >= off) inc += y;
+    }
+    if (k < nk) {
+        cbeg[k] = b;
+        coff[k] = inc - n;
+    }
+    if (k == nk - 1) coff[nk] = inc;
 }
 
 __device__ __forceinline__ int owner_find(const int *coff, int nk, int i) {  // last k with coff[k] <= i
@@ -444,19 +454,24 @@ __device__ __forceinline__ int owner_find(const int *coff, int nk, int i) {  // 
     return lo;
 }
 
-// Exclusive scan over a KBN_OWN_BLOCK-thread workgroup (total to all).
-__device__ __forceinline__ int block_scan_own(int x, int *wsum, int &total) {
+// Exclusive scan over the threads of one walk (total to all).
+template <int W>
+__device__ __forceinline__ int walk_scan(int x, int *wsum, int &total) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     int inc = x;
     for (int o = 1; o < 64; o <<= 1) {
         const int y = __shfl_up(inc, o, 64);
         if (lane >= o) inc += y;
     }
+    if constexpr (W == 1) {
+        total = __shfl(inc, 63, 64);
+        return inc - x;
+    }
     if (lane == 63) wsum[wid] = inc;
     lds_barrier();
     int wpre = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < KBN_OWN_BLOCK / 64; ++w) {
+    for (int w = 0; w < W; ++w) {
         const int ws = wsum[w];
         if (w < wid) wpre += ws;
         tot += ws;
@@ -466,13 +481,14 @@ __device__ __forceinline__ int block_scan_own(int x, int *wsum, int &total) {
     return wpre + inc - x;
 }
 
-// The candidate walk of owner tile t shared by the count and write kernels:
-// each step hands a thread KBN_OWN_ILP consecutive walk positions (all loads
-// issued before the tests), and the caller folds the hits in walk order.
-template <int D, class F>
+// The candidate walk of owner tile t: each step hands a thread KBN_OWN_ILP
+// consecutive walk positions (all loads issued before the tests), and the
+// caller folds the hits in walk order.
+template <int D, int W, class F>
 __device__ __forceinline__ void owner_walk(const OwnerGeom &o, int t, int64_t M, const int *__restrict__ cell,
                                            const float *__restrict__ frac, const int *__restrict__ toff,
                                            int *cbeg, int *coff, F &&fold) {
+    const int tid = threadIdx.x & (64 * W - 1);
     int lo[3], hi[3], first[3], num[3];
     owner_span<D>(o, t, lo, hi, first, num);
     int ncand = 1;
@@ -480,17 +496,17 @@ __device__ __forceinline__ void owner_walk(const OwnerGeom &o, int t, int64_t M,
     for (int d = 0; d < D; ++d) ncand *= num[d];
     for (int k0 = 0; k0 < ncand; k0 += KBN_OWN_MAXC) {
         const int nk = min(KBN_OWN_MAXC, ncand - k0);
-        __syncthreads();
-        owner_stage<D>(o, first, num, k0, nk, toff, cbeg, coff);
-        __syncthreads();
+        walk_sync<W>();
+        if (tid < 64) owner_stage<D>(o, first, num, k0, nk, toff, cbeg, coff, tid);
+        walk_sync<W>();
         const int tot = coff[nk];
-        for (int i0 = 0; i0 < tot; i0 += KBN_OWN_BLOCK * KBN_OWN_ILP) {
+        for (int i0 = 0; i0 < tot; i0 += 64 * W * KBN_OWN_ILP) {
             int p[KBN_OWN_ILP], rel[KBN_OWN_ILP][3];
             float fr[KBN_OWN_ILP][3];
             bool hit[KBN_OWN_ILP];
 #pragma unroll
             for (int u = 0; u < KBN_OWN_ILP; ++u) {
-                const int i = i0 + (int)threadIdx.x * KBN_OWN_ILP + u;
+                const int i = i0 + tid * KBN_OWN_ILP + u;
                 const bool in = i < tot;
                 const int k = owner_find(coff, nk, in ? i : 0);
                 p[u] = in ? cbeg[k] + i - coff[k] : -1;
@@ -560,38 +576,64 @@ k_owner_count(OwnerGeom o, int64_t M, const int *__restrict__ cell, const float 
     }
 }
 
-// Entries and their records of every owner tile (one workgroup per tile,
-// the tiles with most entries dispatched first): the reaching samples of
-// the candidate walk, compacted in walk order.
+// The reaching samples of tile t's candidate walk, compacted in walk order from
+// entry `run` on, with their records.
+template <int D, int W>
+__device__ __forceinline__ void owner_write_tile(const OwnerGeom &o, int t, int run, int64_t M,
+                                                 const int *__restrict__ cell, const float *__restrict__ frac,
+                                                 const int *__restrict__ toff, const int *__restrict__ order,
+                                                 int *__restrict__ rec_p, int *__restrict__ rec_q,
+                                                 int2 *__restrict__ rec_t, int *cbeg, int *coff, int *wsum) {
+    owner_walk<D, W>(o, t, M, cell, frac, toff, cbeg, coff,
+                     [&](const int *p, const bool *hit, int (*rel)[3], float (*fr)[3]) {
+                         int h = 0;
+#pragma unroll
+                         for (int u = 0; u < KBN_OWN_ILP; ++u) h += hit[u] ? 1 : 0;
+                         int total;
+                         int e = run + walk_scan<W>(h, wsum, total);
+#pragma unroll
+                         for (int u = 0; u < KBN_OWN_ILP; ++u) {
+                             if (!hit[u]) continue;
+                             rec_p[e] = p[u];
+                             rec_q[e] = order[p[u]];
+#pragma unroll
+                             for (int d = 0; d < D; ++d)
+                                 rec_t[(int64_t)e * D + d] = make_int2(rel[u][d], __float_as_int(fr[u][d]));
+                             ++e;
+                         }
+                         run += total;
+                     });
+}
+
+// Entries and their records of every owner tile, the tiles with most entries
+// first: workgroups 0 .. hot - 1 take one tile of more than `few` entries each, the
+// others four tiles of fewer, one per wavefront.  Bound by the chain of loads of
+// a walk, so by the walks in flight: with a workgroup for each of the 262144 tiles
+// of 256^3 50000 samples took 1060 us of an index pass of 1280, which is 450 now,
+// and 3M samples 1670 of 2930 (2610).
 template <int D>
 __global__ void __launch_bounds__(KBN_OWN_BLOCK)
-k_owner_write(OwnerGeom o, int64_t M, const int *__restrict__ cell, const float *__restrict__ frac,
+k_owner_write(OwnerGeom o, int hot, int few, int64_t M, const int *__restrict__ cell, const float *__restrict__ frac,
               const int *__restrict__ toff, const int *__restrict__ order, const int *__restrict__ ooff,
               const int *__restrict__ otile_order, int *__restrict__ rec_p, int *__restrict__ rec_q,
               int2 *__restrict__ rec_t) {
-    __shared__ int cbeg[KBN_OWN_MAXC], coff[KBN_OWN_MAXC + 1];
-    __shared__ int wsum[KBN_OWN_BLOCK / 64];
-    const int t = otile_order[blockIdx.x];  // tiles with the most entries first
-    int run = ooff[t];
-    owner_walk<D>(o, t, M, cell, frac, toff, cbeg, coff,
-                  [&](const int *p, const bool *hit, int (*rel)[3], float (*fr)[3]) {
-                      int h = 0;
-#pragma unroll
-                      for (int u = 0; u < KBN_OWN_ILP; ++u) h += hit[u] ? 1 : 0;
-                      int total;
-                      int e = run + block_scan_own(h, wsum, total);
-#pragma unroll
-                      for (int u = 0; u < KBN_OWN_ILP; ++u) {
-                          if (!hit[u]) continue;
-                          rec_p[e] = p[u];
-                          rec_q[e] = order[p[u]];
-#pragma unroll
-                          for (int d = 0; d < D; ++d)
-                              rec_t[(int64_t)e * D + d] = make_int2(rel[u][d], __float_as_int(fr[u][d]));
-                          ++e;
-                      }
-                      run += total;
-                  });
+    constexpr int W = KBN_OWN_BLOCK / 64;
+    __shared__ int cbeg[W][KBN_OWN_MAXC], coff[W][KBN_OWN_MAXC + 1];
+    __shared__ int wsum[W];
+    if ((int)blockIdx.x < hot) {
+        const int t = otile_order[blockIdx.x];
+        const int run = ooff[t];
+        if (ooff[t + 1] - run <= few) return;
+        owner_write_tile<D, W>(o, t, run, M, cell, frac, toff, order, rec_p, rec_q, rec_t, cbeg[0], coff[0], wsum);
+    } else {
+        const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+        const int k = ((int)blockIdx.x - hot) * W + w;
+        if (k >= o.ntiles_own) return;
+        const int t = otile_order[k];
+        const int run = ooff[t], n = ooff[t + 1] - run;
+        if (n == 0 || n > few) return;
+        owner_write_tile<D, 1>(o, t, run, M, cell, frac, toff, order, rec_p, rec_q, rec_t, cbeg[w], coff[w], wsum);
+    }
 }
 
 // Order of the tiles: bins (2^k, 2^(k+1)] of their entry count, larger first, so
@@ -1037,6 +1079,15 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
         const hipError_t e = allow_large_lds(3 * sizeof(int) * (size_t)std::min(n, KBN_OWN_LDS));
         if (e != hipSuccess) return e;
     }
+    // Entries up to which one wavefront writes a tile: more in 3D, where a tile has
+    // fewer candidates per entry (8-cell sort tiles, 32-cell ones in 2D).  With
+    // few tiles a workgroup each leaves room (128^2, 1024 tiles, 9000 samples 74 us
+    // against 82; 4096 110 and 115; 6400 126 and 118).  A power of two, so that the
+    // tiles above it come first (owner_key); there are at most M 2^D / few of them.
+    const int few = n <= 4096 ? 0 : (g.D == 3 ? 64 : 16);
+    const int hot = (int)std::min<int64_t>(n, few ? (M << g.D) / few : n);
+    const int waves = few ? (n + KBN_OWN_BLOCK / 64 - 1) / (KBN_OWN_BLOCK / 64) : 0;
+    const dim3 wgrid((unsigned)(hot + waves));
     switch (g.D) {
 #define KBN_OWN(d)                                                                                     \
     case d:                                                                                            \
@@ -1054,8 +1105,10 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
             k_owner_place<<<dim3(nb), dim3(1024), 0, s>>>(n, nb, ocount, scratch, ooff, otile_order,   \
                                                           swork, scomb);                               \
         }                                                                                              \
-        k_owner_write<d><<<dim3(n), dim3(KBN_OWN_BLOCK), 0, s>>>(o, M, cell, frac, toff, order, ooff,  \
-                                                                 otile_order, rec_p, rec_q, rec_t);    \
+        if (M > 0)                                                                                     \
+            k_owner_write<d><<<wgrid, dim3(KBN_OWN_BLOCK), 0, s>>>(o, hot, few, M, cell, frac, toff,   \
+                                                                   order, ooff, otile_order, rec_p,    \
+                                                                   rec_q, rec_t);                      \
         break;
         KBN_OWN(1) KBN_OWN(2) KBN_OWN(3)
 #undef KBN_OWN
