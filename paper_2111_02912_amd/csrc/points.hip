@@ -971,36 +971,45 @@ hipError_t allow_large_lds(size_t bytes) {
     return once;
 }
 
+namespace {
+
+// Histogram chunks of M > 0 samples: at most 4096 samples per chunk (one
+// wavefront ranks a chunk in steps of 64); otherwise as many chunks as keep the
+// count matrix within one workgroup's scan, and at least 256 samples per chunk.
+// Where 4096 samples already take the multi-workgroup scan, smaller chunks cost
+// it little and fill the GPU, until the strided counts of a million entries cost
+// more (index pass of 48^3 with 65536 samples 330 -> 264 us, 75 x 90 x 64 with
+// 150001 447 -> 391, of it histogram 35 -> 17 and scatter 72 -> 38; 262144
+// entries 279 and 433 us; 96^3 with 1M samples has 13825 bins and stays).
+// Never fewer for more samples, which the chunks rounded to 64 samples may be.
+int64_t most_chunks(int64_t M, int64_t nbins) {
+    const int64_t nmin = (M + 4095) / 4096;
+    const int64_t nsmall = std::max<int64_t>(1, KBN_SCAN_SMALL / nbins);
+    const int64_t n256 = std::max<int64_t>(1, M / 256);
+    return nmin <= nsmall ? std::max(nmin, std::min(nsmall, n256))
+                          : std::max(nmin, std::min(n256, KBN_SCAN_COUNTS / nbins));
+}
+
+}  // namespace
+
 int kbn_points_chunks(int64_t M, int ntiles, int *chunk) {
-    const int64_t nbins = (int64_t)ntiles + 1;
     if (M <= 0) {
         *chunk = 64;
         return 0;
     }
-    // at most 4096 samples per chunk (one wavefront ranks a chunk in steps of
-    // 64); otherwise as many chunks as keep the count matrix within one
-    // workgroup's scan, and at least 256 samples per chunk.  Where 4096 samples
-    // already take the multi-workgroup scan, smaller chunks cost it little and
-    // fill the GPU, until the strided counts of a million entries cost more
-    // (index pass of 48^3 with 65536 samples 330 -> 264 us, 75 x 90 x 64 with
-    // 150001 447 -> 391, of it histogram 35 -> 17 and scatter 72 -> 38; 262144
-    // entries 279 and 433 us; 96^3 with 1M samples has 13825 bins and stays).
-    const int64_t nmin = (M + 4095) / 4096;
-    const int64_t nsmall = std::max<int64_t>(1, KBN_SCAN_SMALL / nbins);
-    const int64_t n256 = std::max<int64_t>(1, M / 256);
-    const int64_t want = nmin <= nsmall ? std::max(nmin, std::min(nsmall, n256))
-                                        : std::max(nmin, std::min(n256, KBN_SCAN_COUNTS / nbins));
+    const int64_t want = most_chunks(M, (int64_t)ntiles + 1);
     int64_t c = (M + want - 1) / want;
     c = (c + 63) / 64 * 64;
     *chunk = (int)c;
     return (int)((M + c - 1) / c);
 }
 
+// The count matrix and the three-phase scan's span sums.  Sized by most_chunks,
+// so that the buffers of M samples hold those of every smaller M too.
 int64_t kbn_points_owner_base(int64_t M, int ntiles) {
-    int chunk;
-    const int64_t nch = kbn_points_chunks(M, ntiles, &chunk);
-    const int64_t S = nch * ((int64_t)ntiles + 1);
-    return S + S / KBN_SCAN_SPAN + 2;  // the count matrix and the three-phase scan's span sums
+    const int64_t nbins = (int64_t)ntiles + 1;
+    const int64_t S = M > 0 ? most_chunks(M, nbins) * nbins : 0;
+    return S + S / KBN_SCAN_SPAN + 2;
 }
 
 int64_t kbn_points_counts_size(int64_t M, int ntiles, int ntiles_own) {

@@ -33,6 +33,9 @@ int main(int, char **v) {
         const KbnGatherShape sh = kbn_gather_shape(g, std::atoll(v[4]), std::atoi(v[5]), std::atoi(v[6]));
         std::printf("%d %d %d %d", (int)sh.staged, (int)sh.blocks, sh.cg, sh.groups);
     }
+    if (!std::strcmp(v[1], "counts"))  // sort tiles, owner tiles, M..: integers of the index pass
+        for (int i = 4; v[i]; ++i)
+            std::printf("%lld ", (long long)kbn_points_counts_size(std::atoll(v[i]), std::atoi(v[2]), std::atoi(v[3])));
     std::printf("\n");
 }
 """
@@ -83,6 +86,15 @@ def test_gather_groups_keep_pairs_once_the_gpu_is_filled(rules, M, nbc, nw, K, T
     assert groups <= fill or cg // nw >= 4
     if nbc >= 4 * 32:  # many pairs: several rounds of workgroups
         assert blocks * groups >= min(8192, blocks * nbc // 8)
+
+
+@pytest.mark.parametrize("tiles", [(6992, 7000), (100, 100), (256, 4096), (13824, 13824), (32768, 110592)])
+def test_buffers_of_more_samples_hold_fewer(rules, tiles):
+    """A plan that goes back and forth between sample counts keeps the buffers of
+    the larger one."""
+    M = sorted({int(1.07 ** k) for k in range(30, 240)} | {152576, 160000} | {1 << k for k in range(8, 24)})
+    n = rules("counts", *tiles, *M)
+    assert n == sorted(n)
 
 
 def test_launches_compute_no_splits():
