@@ -5,6 +5,10 @@ split into work items (128, doubled until 256 slots hold them), tiles
 without entries.  Adjoints against the exact NUDFT at a sample of pixels, and
 against plans with larger owner tiles, whose cells add the same FP32 products
 in another order (2e-6)."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -54,3 +58,50 @@ def test_adjoint_of_owner_lists(N, big, kind):
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
     pix = np.sort(W.rng(26).choice(int(np.prod(N)), 400, replace=False))
     assert ndft.rel_l2(got.reshape(1, -1)[:, pix], ndft.adjoint(om, y[:, 0], N, pix=pix)) < 2e-5
+
+
+# More owner tiles than a grid has rows: default 3D plans from K = 321 on (the
+# matrix-core spread strides over its work items), and tiles of 9 cells, which
+# become larger instead.  Samples at the ends of every axis reach the last items.
+@pytest.mark.parametrize("nch", [1, 2, 3, 5])
+def test_adjoint_of_more_tiles_than_grid_rows(nch):
+    from paper_2111_02912_amd.nufft import KbNufft
+    dev = torch.device("cuda", 0)
+    N, M = (163, 162, 164), 3000
+    print(f"more tiles than rows N={N} channels={nch}", flush=True)
+    om = W.uniform_random(M, 3, seed=31)
+    om[::7] = np.pi * np.sign(om[::7]) * (1 - 1e-3)
+    y = W.complex_normal((nch, 1, M), 32)
+    pix = np.sort(W.rng(33).choice(int(np.prod(N)), 300, replace=False))
+    want = ndft.adjoint(om, y[:, 0], N, pix=pix)
+    for kw in ({}, dict(spread_tile=9)):
+        p = KbNufft(N, device=dev, **kw)
+        p.set_points(torch.from_numpy(om).to(dev))
+        got = p.adjoint(torch.from_numpy(y).to(dev)).cpu().numpy()
+        p.close()
+        assert ndft.rel_l2(got.reshape(nch, -1)[:, pix], want) < 2e-5
+
+
+def test_scatter_spread_strides_over_work_items(tmp_path):
+    """The scatter kernel (KBN_SPREAD_OS=0, read once per process) with more work
+    items than a grid has rows."""
+    print("scatter spread with more items than rows", flush=True)
+    N, M = (163, 162, 164), 2000
+    om = W.uniform_random(M, 3, seed=41)
+    om[::5] = np.pi * np.sign(om[::5]) * (1 - 1e-3)
+    y = W.complex_normal((2, 1, M), 42)
+    np.savez(tmp_path / "in.npz", om=om, y=y)
+    code = f"""
+import numpy as np, torch
+from paper_2111_02912_amd.nufft import KbNufft
+d = np.load(r"{tmp_path / 'in.npz'}")
+p = KbNufft({N}, device=torch.device("cuda", 0))
+p.set_points(torch.from_numpy(d["om"]).cuda())
+np.save(r"{tmp_path / 'out.npy'}", p.adjoint(torch.from_numpy(d["y"]).cuda()).cpu().numpy())
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=100, cwd=root,
+                   env=dict(os.environ, KBN_SPREAD_OS="0"))
+    got = np.load(tmp_path / "out.npy")
+    pix = np.sort(W.rng(43).choice(int(np.prod(N)), 300, replace=False))
+    assert ndft.rel_l2(got.reshape(2, -1)[:, pix], ndft.adjoint(om, y[:, 0], N, pix=pix)) < 2e-5
