@@ -1161,11 +1161,16 @@ int plan_setup(kbn_plan p, int D, const int64_t *N, const kbn_opts *opts) {
     if (ntiles > KBN_MAX_TILES) return fail(KBN_ERR_UNSUPPORTED, "too many tiles; use larger tiles");
     p->ntiles = (int)ntiles;
     // spread owner tiles: even splits of each axis near the preferred edge, at
-    // least J - 1 wide so that a J-tap footprint meets at most two per axis
+    // least J - 1 wide so that a J-tap footprint meets at most two per axis.  More
+    // than KBN_MAX_TILES of them only where the matrix-core spread takes them and
+    // the preferred edge is its 8 cells already: smaller tiles fill its operands
+    // less (96^3, J = 4, one channel: 4-cell tiles 319 us, 8-cell 132), and the other
+    // spreads then do better with larger ones.
     int64_t ntiles_own = 1;
     int defown = o.spread_tile > 0 ? std::max(J, o.spread_tile) : (D == 1 ? 128 : 8);
     for (;;) {
         ntiles_own = 1;
+        int most = 1;
         for (int d = 0; d < D; ++d) {
             const int K = p->K[d];
             int n = std::max(1, (K + defown - 1) / defown);
@@ -1173,9 +1178,11 @@ int plan_setup(kbn_plan p, int D, const int64_t *N, const kbn_opts *opts) {
             p->To[d] = (K + n - 1) / n;
             p->nto[d] = n;
             ntiles_own *= n;
+            most = std::max(most, p->To[d]);
         }
-        if (ntiles_own <= KBN_MAX_OWN || defown >= KBN_MAX_K) break;
-        defown += 4;
+        if (ntiles_own <= KBN_MAX_TILES || defown >= KBN_MAX_K) break;
+        if (D >= 2 && most <= 8 && defown >= 8 && ntiles_own <= KBN_MAX_OWN) break;
+        defown = defown < 8 ? 8 : defown + 4;
     }
     if (ntiles_own > KBN_MAX_OWN) {
         return fail(KBN_ERR_UNSUPPORTED, "too many spread tiles");

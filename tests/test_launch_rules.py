@@ -1,5 +1,6 @@
 """Launch shapes, which the host computes for every call: a small program over the
 library's internal header prints them (no GPU call is made here)."""
+import ctypes
 import os
 import shutil
 import subprocess
@@ -95,6 +96,20 @@ def test_buffers_of_more_samples_hold_fewer(rules, tiles):
     M = sorted({int(1.07 ** k) for k in range(30, 240)} | {152576, 160000} | {1 << k for k in range(8, 24)})
     n = rules("counts", *tiles, *M)
     assert n == sorted(n)
+
+
+@pytest.mark.parametrize("tile,as_tile", [(9, 13), (10, 14), (4, 8), (7, 8), (8, 8), (16, 16)])
+def test_only_matrix_core_tiles_may_be_many(tile, as_tile):
+    """384^3 grids: owner tiles that no matrix-core spread takes stay below the
+    rows of a grid, and those smaller than its 8 cells grow to them.  (A plan's
+    bytes count its tiles; J = 4 lets a tile have 4 cells.)"""
+    def footprint(t):
+        o, out = _lib.KbnOpts(), ctypes.c_int64()
+        o.sigma, o.J, o.spread_tile = 2.0, 4, t
+        _lib.check(_lib.lib().kbn_plan_footprint(3, (ctypes.c_int64 * 3)(192, 192, 192), ctypes.byref(o), 10, 1, 1, 0,
+                                                 ctypes.byref(out)), "kbn_plan_footprint")
+        return out.value
+    assert footprint(tile) == footprint(as_tile)
 
 
 def test_launches_compute_no_splits():
