@@ -437,170 +437,167 @@ __host__ __device__ inline int spread_plane(int psize) { return psize + ((6 - ps
 //   A = 1: lanes = (tap along the last axis) x (64 / J channels)
 //   A = 2: lanes = (taps along the last two axes) x (64 / J^2 channels)
 template <int D, int J, int A>
-__global__ void __launch_bounds__(KBN_BLOCK) k_spread(KbnGeom g, KbnSpreadArgs a, int cw, int nwave) {
+__global__ void __launch_bounds__(KBN_BLOCK) k_spread(KbnGeom g, KbnSpreadArgs a, int cw, int nwave, int wk0) {
     constexpr int EB = KBN_SPREAD_EB;
     constexpr int LANES_TAP = A == 1 ? J : J * J;
     constexpr int NEG = -(1 << 28);                // offset of a tap outside the tile
     extern __shared__ float smem[];
-    const int nwork = a.scounts[0];
-    // a grid smaller than the work list strides over it
-    for (int wk = blockIdx.y; wk < nwork; wk += gridDim.y) {
-        const int tile = a.swork[4 * wk];
-        const int slot = a.swork[4 * wk + 3];
-        const int ngroup = nwave * cw;                 // channels per workgroup
-        const int ch0 = blockIdx.x * ngroup;
-        const int nchg = min(ngroup, a.nch - ch0);
-        int a0[KBN_MAX_D], te[KBN_MAX_D], pt[KBN_MAX_D];
-        {
-            int rem = tile;
-            for (int d = D - 1; d >= 0; --d) {
-                const int tc = rem % g.nto[d];
-                rem /= g.nto[d];
-                a0[d] = own_lo(tc, g.K[d], g.nto[d]);
-                te[d] = own_lo(tc + 1, g.K[d], g.nto[d]) - a0[d];
-                pt[d] = acc_pitch(d, te[d]);
-            }
-        }
-        int psize = 1, tsize = 1;
-        int stride[KBN_MAX_D];
+    const int wk = wk0 + blockIdx.y;               // work item
+    if (wk >= a.scounts[0]) return;
+    const int tile = a.swork[4 * wk];
+    const int slot = a.swork[4 * wk + 3];
+    const int ngroup = nwave * cw;                 // channels per workgroup
+    const int ch0 = blockIdx.x * ngroup;
+    const int nchg = min(ngroup, a.nch - ch0);
+    int a0[KBN_MAX_D], te[KBN_MAX_D], pt[KBN_MAX_D];
+    {
+        int rem = tile;
         for (int d = D - 1; d >= 0; --d) {
-            stride[d] = psize;
-            psize *= pt[d];
-            tsize *= te[d];
+            const int tc = rem % g.nto[d];
+            rem /= g.nto[d];
+            a0[d] = own_lo(tc, g.K[d], g.nto[d]);
+            te[d] = own_lo(tc + 1, g.K[d], g.nto[d]) - a0[d];
+            pt[d] = acc_pitch(d, te[d]);
         }
-        const int plane = spread_plane(psize);         // float2 per channel plane
-        float2 *acc = reinterpret_cast<float2 *>(smem);
-        // per staged entry and axis tap: (offset in the tile accumulator or NEG
-        // when outside the tile, as int bits; weight)
-        float2 *ent_ow = reinterpret_cast<float2 *>(acc + (size_t)ngroup * plane);  // [EB][D][J]
-        int *ent_p = reinterpret_cast<int *>(ent_ow + EB * D * J);
-        float2 *ent_y = reinterpret_cast<float2 *>(ent_p + EB);  // [ngroup][EB + 1]
-        const int nthr = nwave * 64;
-        if (wk != (int)blockIdx.y) __syncthreads();  // the previous item's tile is written
-        for (int i = threadIdx.x; i < nchg * plane; i += nthr) acc[i] = make_float2(0.f, 0.f);
+    }
+    int psize = 1, tsize = 1;
+    int stride[KBN_MAX_D];
+    for (int d = D - 1; d >= 0; --d) {
+        stride[d] = psize;
+        psize *= pt[d];
+        tsize *= te[d];
+    }
+    const int plane = spread_plane(psize);         // float2 per channel plane
+    float2 *acc = reinterpret_cast<float2 *>(smem);
+    // per staged entry and axis tap: (offset in the tile accumulator or NEG
+    // when outside the tile, as int bits; weight)
+    float2 *ent_ow = reinterpret_cast<float2 *>(acc + (size_t)ngroup * plane);  // [EB][D][J]
+    int *ent_p = reinterpret_cast<int *>(ent_ow + EB * D * J);
+    float2 *ent_y = reinterpret_cast<float2 *>(ent_p + EB);  // [ngroup][EB + 1]
+    const int nthr = nwave * 64;
+    for (int i = threadIdx.x; i < nchg * plane; i += nthr) acc[i] = make_float2(0.f, 0.f);
 
-        const int lane = threadIdx.x & 63;
-        const int wave = threadIdx.x >> 6;
-        const int cc = lane / LANES_TAP;
-        const int jin = lane - cc * LANES_TAP;
-        const int cl = wave * cw + cc;                 // channel of this lane within the group
-        const bool lane_on = cc < cw && cl < nchg;
-        const int jb = A == 1 ? jin : jin % J;         // tap along the last axis
-        const int ja = A == 1 ? 0 : jin / J;           // tap along the axis before it (A == 2)
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int cc = lane / LANES_TAP;
+    const int jin = lane - cc * LANES_TAP;
+    const int cl = wave * cw + cc;                 // channel of this lane within the group
+    const bool lane_on = cc < cw && cl < nchg;
+    const int jb = A == 1 ? jin : jin % J;         // tap along the last axis
+    const int ja = A == 1 ? 0 : jin / J;           // tap along the axis before it (A == 2)
 
-        const int e0 = a.swork[4 * wk + 1], e1 = a.swork[4 * wk + 2];
-        for (int eb = e0; eb < e1; eb += EB) {
-            const int n = min(EB, e1 - eb);
-            __syncthreads();  // previous batch fully consumed (and acc zeroed)
-            if ((int)threadIdx.x < n) {
-                // stage entry t: precomputed record -> per-axis tap offsets and weights
-                const int t = threadIdx.x;
-                const int e = eb + t;
-                ent_p[t] = a.rec_p[e];
+    const int e0 = a.swork[4 * wk + 1], e1 = a.swork[4 * wk + 2];
+    for (int eb = e0; eb < e1; eb += EB) {
+        const int n = min(EB, e1 - eb);
+        __syncthreads();  // previous batch fully consumed (and acc zeroed)
+        if ((int)threadIdx.x < n) {
+            // stage entry t: precomputed record -> per-axis tap offsets and weights
+            const int t = threadIdx.x;
+            const int e = eb + t;
+            ent_p[t] = a.rec_p[e];
 #pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    const int2 tr = a.rec_t[(int64_t)e * D + d];
-                    const int l = tr.x;
-                    float w[J];
-                    kb_weights<J>(__int_as_float(tr.y), g.coef, w);
+            for (int d = 0; d < D; ++d) {
+                const int2 tr = a.rec_t[(int64_t)e * D + d];
+                const int l = tr.x;
+                float w[J];
+                kb_weights<J>(__int_as_float(tr.y), g.coef, w);
 #pragma unroll
-                    for (int j = 0; j < J; ++j) {
-                        int loc = l + j;
-                        if (loc >= g.K[d]) loc -= g.K[d];
-                        const int off = loc < te[d] ? loc * stride[d] : NEG;
-                        ent_ow[(t * D + d) * J + j] = make_float2(__int_as_float(off), w[j]);
-                    }
-                }
-            }
-            __syncthreads();
-            // k-space values of the staged entries: EB entries x channels, with
-            // nthr / EB channels per pass (nthr is a multiple of EB)
-            {
-                const int i = threadIdx.x % EB;
-                const int cstep = nthr / EB;
-                if (i < n) {
-                    const int pi = ent_p[i];
-                    for (int c = threadIdx.x / EB; c < nchg; c += cstep)
-                        ent_y[c * (EB + 1) + i] = a.ys[(int64_t)(ch0 + c) * a.M + pi];
-                }
-            }
-            __syncthreads();
-            if (lane_on) {
-                float2 *accc = acc + (size_t)cl * plane;
-                const float2 *yc = ent_y + cl * (EB + 1);
-                for (int i = 0; i < n; ++i) {
-                    const float2 *owi = ent_ow + i * D * J;
-                    const float2 ib = owi[(D - 1) * J + jb];
-                    int inner = __float_as_int(ib.x);
-                    float wv = ib.y;
-                    if (A == 2) {
-                        const float2 ia = owi[(D - 2) * J + ja];
-                        inner += __float_as_int(ia.x);
-                        wv *= ia.y;
-                    }
-                    const float2 yv = yc[i];
-                    const float2 v = make_float2(wv * yv.x, wv * yv.y);
-                    constexpr int NO = D - A == 0 ? 1 : (D - A == 1 ? J : J * J);  // outer taps
-                    float2 o[NO];
-                    int cidx[NO];
-                    float wo[NO];
-#pragma unroll
-                    for (int t = 0; t < NO; ++t) {
-                        int off = inner;
-                        float wt = 1.f;
-                        if (D - A >= 1) {
-                            const int j0 = D - A == 1 ? t : t / J;
-                            const float2 r0 = owi[j0];
-                            off += __float_as_int(r0.x);
-                            wt = r0.y;
-                        }
-                        if (D - A == 2) {
-                            const int j1 = t % J;
-                            const float2 r1 = owi[J + j1];
-                            off += __float_as_int(r1.x);
-                            wt *= r1.y;
-                        }
-                        cidx[t] = off;
-                        wo[t] = wt;
-                        if (off >= 0) o[t] = accc[off];
-                    }
-#pragma unroll
-                    for (int t = 0; t < NO; ++t)
-                        if (cidx[t] >= 0)
-                            accc[cidx[t]] = make_float2(fmaf(wo[t], v.x, o[t].x), fmaf(wo[t], v.y, o[t].y));
+                for (int j = 0; j < J; ++j) {
+                    int loc = l + j;
+                    if (loc >= g.K[d]) loc -= g.K[d];
+                    const int off = loc < te[d] ? loc * stride[d] : NEG;
+                    ent_ow[(t * D + d) * J + j] = make_float2(__int_as_float(off), w[j]);
                 }
             }
         }
         __syncthreads();
-        // write the owned tile of every channel in the group: to the grid, or
-        // (tile split into several work items) to this item's partial slot.
-        // Threads cover (channel, row) pairs x last-axis columns; a row is one
-        // index tuple of the leading axes.
-        int nrows = 1;
-        for (int d = 0; d + 1 < D; ++d) nrows *= te[d];
-        const int tl = te[D - 1];
-        int pstride = 1;
-        for (int d = 0; d < D; ++d) pstride *= g.To[d];
-        for (int idx = threadIdx.x; idx < nchg * nrows * tl; idx += nthr) {
-            const int cr = idx / tl;           // (channel, row) pair
-            const int col = idx - cr * tl;
-            const int c = cr / nrows;
-            const int r = cr - c * nrows;
-            int rem = r, lo = col;
-            int64_t goff = 0, gstride = g.K[D - 1];
-            for (int d = D - 2; d >= 0; --d) {
-                const int l = D == 2 ? rem : rem % te[d];
-                rem = D == 2 ? 0 : rem / te[d];
-                lo += l * stride[d];
-                goff += (int64_t)(a0[d] + l) * gstride;
-                gstride *= g.K[d];
+        // k-space values of the staged entries: EB entries x channels, with
+        // nthr / EB channels per pass (nthr is a multiple of EB)
+        {
+            const int i = threadIdx.x % EB;
+            const int cstep = nthr / EB;
+            if (i < n) {
+                const int pi = ent_p[i];
+                for (int c = threadIdx.x / EB; c < nchg; c += cstep)
+                    ent_y[c * (EB + 1) + i] = a.ys[(int64_t)(ch0 + c) * a.M + pi];
             }
-            const float2 v = acc[(size_t)c * plane + lo];
-            if (slot >= 0)
-                a.partial[((int64_t)slot * a.nch + ch0 + c) * pstride + r * tl + col] = v;
-            else
-                a.grid[(int64_t)(ch0 + c) * a.gsize + goff + a0[D - 1] + col] = v;
         }
+        __syncthreads();
+        if (lane_on) {
+            float2 *accc = acc + (size_t)cl * plane;
+            const float2 *yc = ent_y + cl * (EB + 1);
+            for (int i = 0; i < n; ++i) {
+                const float2 *owi = ent_ow + i * D * J;
+                const float2 ib = owi[(D - 1) * J + jb];
+                int inner = __float_as_int(ib.x);
+                float wv = ib.y;
+                if (A == 2) {
+                    const float2 ia = owi[(D - 2) * J + ja];
+                    inner += __float_as_int(ia.x);
+                    wv *= ia.y;
+                }
+                const float2 yv = yc[i];
+                const float2 v = make_float2(wv * yv.x, wv * yv.y);
+                constexpr int NO = D - A == 0 ? 1 : (D - A == 1 ? J : J * J);  // outer taps
+                float2 o[NO];
+                int cidx[NO];
+                float wo[NO];
+#pragma unroll
+                for (int t = 0; t < NO; ++t) {
+                    int off = inner;
+                    float wt = 1.f;
+                    if (D - A >= 1) {
+                        const int j0 = D - A == 1 ? t : t / J;
+                        const float2 r0 = owi[j0];
+                        off += __float_as_int(r0.x);
+                        wt = r0.y;
+                    }
+                    if (D - A == 2) {
+                        const int j1 = t % J;
+                        const float2 r1 = owi[J + j1];
+                        off += __float_as_int(r1.x);
+                        wt *= r1.y;
+                    }
+                    cidx[t] = off;
+                    wo[t] = wt;
+                    if (off >= 0) o[t] = accc[off];
+                }
+#pragma unroll
+                for (int t = 0; t < NO; ++t)
+                    if (cidx[t] >= 0)
+                        accc[cidx[t]] = make_float2(fmaf(wo[t], v.x, o[t].x), fmaf(wo[t], v.y, o[t].y));
+            }
+        }
+    }
+    __syncthreads();
+    // write the owned tile of every channel in the group: to the grid, or
+    // (tile split into several work items) to this item's partial slot.
+    // Threads cover (channel, row) pairs x last-axis columns; a row is one
+    // index tuple of the leading axes.
+    int nrows = 1;
+    for (int d = 0; d + 1 < D; ++d) nrows *= te[d];
+    const int tl = te[D - 1];
+    int pstride = 1;
+    for (int d = 0; d < D; ++d) pstride *= g.To[d];
+    for (int idx = threadIdx.x; idx < nchg * nrows * tl; idx += nthr) {
+        const int cr = idx / tl;           // (channel, row) pair
+        const int col = idx - cr * tl;
+        const int c = cr / nrows;
+        const int r = cr - c * nrows;
+        int rem = r, lo = col;
+        int64_t goff = 0, gstride = g.K[D - 1];
+        for (int d = D - 2; d >= 0; --d) {
+            const int l = D == 2 ? rem : rem % te[d];
+            rem = D == 2 ? 0 : rem / te[d];
+            lo += l * stride[d];
+            goff += (int64_t)(a0[d] + l) * gstride;
+            gstride *= g.K[d];
+        }
+        const float2 v = acc[(size_t)c * plane + lo];
+        if (slot >= 0)
+            a.partial[((int64_t)slot * a.nch + ch0 + c) * pstride + r * tl + col] = v;
+        else
+            a.grid[(int64_t)(ch0 + c) * a.gsize + goff + a0[D - 1] + col] = v;
     }
 }
 
@@ -1452,11 +1449,16 @@ hipError_t spread_dj(const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
             dim3 pgrid((unsigned)((a.M + KBN_BLOCK - 1) / KBN_BLOCK), (unsigned)a.nch);
             k_permute<<<pgrid, dim3(KBN_BLOCK), 0, s>>>(a.y, a.ys, a.order, a.M);
         }
-        dim3 grid((unsigned)ng, (unsigned)std::min(a.nwork_max, KBN_GRID_Y_MAX));
-        if (sh.A == 1 || D == 1)
-            k_spread<D, J, 1><<<grid, dim3(64 * sh.nwave), sh.lds, s>>>(g, a, sh.cw, sh.nwave);
-        else
-            k_spread<D, J, (D >= 2 ? 2 : 1)><<<grid, dim3(64 * sh.nwave), sh.lds, s>>>(g, a, sh.cw, sh.nwave);
+        // one workgroup row per work item, in several launches beyond the rows of a
+        // grid (a loop or a third grid dimension instead: 1D N = 64 21 -> 23 us, 60 x
+        // 64 x 70 with 12-cell tiles 532 -> 548)
+        for (int wk0 = 0; wk0 < a.nwork_max; wk0 += KBN_GRID_Y_MAX) {
+            const dim3 grid((unsigned)ng, (unsigned)std::min(a.nwork_max - wk0, KBN_GRID_Y_MAX));
+            if (sh.A == 1 || D == 1)
+                k_spread<D, J, 1><<<grid, dim3(64 * sh.nwave), sh.lds, s>>>(g, a, sh.cw, sh.nwave, wk0);
+            else
+                k_spread<D, J, (D >= 2 ? 2 : 1)><<<grid, dim3(64 * sh.nwave), sh.lds, s>>>(g, a, sh.cw, sh.nwave, wk0);
+        }
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;

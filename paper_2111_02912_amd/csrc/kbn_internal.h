@@ -24,7 +24,7 @@
 #define KBN_SPREAD_EB 64   // list entries staged per spread batch
 #define KBN_SPREAD_SEG 128  // list entries per spread work item (doubled if slots run out)
 #define KBN_SPREAD_SMAX 256 // partial-tile slots for tiles split into several work items
-#define KBN_GRID_Y_MAX 65535 // spreads stride over work items beyond this many workgroup rows
+#define KBN_GRID_Y_MAX 65535 // spreads stride over work items, or launch again, beyond this many workgroup rows
 #define KBN_SPREAD_LDS (64 * 1024)  // LDS budget of one spread workgroup
 
 // kernel classes reported by kbn_timing_read (order of kClassNames)
