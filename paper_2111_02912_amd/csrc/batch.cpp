@@ -432,9 +432,13 @@ int kbn_batch_capture(kbn_batch b, void *stream) {
     int rc = issue(b, s);
     if (rc != KBN_OK) return rc;
     KBN_BHIP(hipStreamSynchronize(s), "hipStreamSynchronize");
-    // the eager pass waited for every plan's index pass: note it, so that the
-    // captured calls need not wait on events from outside the capture
-    for (kbn_plan p : b->plans) kbn_internal_points_settle(p);
+    // captured calls cannot wait on events from outside the capture, and of the
+    // eager pass the gathers waited for the sorted samples only: let every
+    // plan's index pass end first
+    for (kbn_plan p : b->plans) {
+        rc = kbn_internal_points_settle(p);
+        if (rc != KBN_OK) return rc;
+    }
     KBN_BHIP(hipStreamBeginCapture(b->origin, hipStreamCaptureModeThreadLocal), "hipStreamBeginCapture");
     rc = issue(b, b->origin);
     hipGraph_t g = nullptr;

@@ -333,8 +333,8 @@ double kbn_internal_cost(kbn_plan p, int B, int C, int jac, int type1);
 uint64_t kbn_internal_epoch(kbn_plan p);  // changes with every kbn_set_points
 // order `s` after the plan's last index pass (which runs on its own stream)
 int kbn_internal_points_wait(kbn_plan p, hipStream_t s);
-// note a finished index pass (before a capture, whose waits cannot name it)
-void kbn_internal_points_settle(kbn_plan p);
+// wait on the host for the index pass to end (before a capture, whose waits cannot name it)
+int kbn_internal_points_settle(kbn_plan p);
 // device memory through the plan's allocator, counted in its footprint
 int kbn_internal_alloc(kbn_plan p, void **ptr, int64_t bytes, hipStream_t s);
 void kbn_internal_free(kbn_plan p, void *ptr, hipStream_t s);

@@ -934,8 +934,10 @@ double kbn_internal_cost(kbn_plan p, int B, int C, int jac, int type1) {
 
 uint64_t kbn_internal_epoch(kbn_plan p) { return p->epoch; }
 int kbn_internal_points_wait(kbn_plan p, hipStream_t s) { return points_wait(p, s); }
-void kbn_internal_points_settle(kbn_plan p) {
-    if (p->points_pending && hipEventQuery(p->points_ready) == hipSuccess) p->points_pending = false;
+int kbn_internal_points_settle(kbn_plan p) {
+    if (p->points_pending) KBN_HIP(hipEventSynchronize(p->points_ready));
+    p->points_pending = false;
+    return KBN_OK;
 }
 
 int kbn_internal_alloc(kbn_plan p, void **ptr, int64_t bytes, hipStream_t s) {

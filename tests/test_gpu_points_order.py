@@ -101,3 +101,39 @@ def test_capture_of_an_adjoint_behind_an_eager_forward():
         out.zero_()
         plan.forward(x)
         torch.cuda.synchronize()
+
+
+def test_capture_behind_a_captured_batch_of_forward_calls():
+    """Capturing a batch ends with its plans' index passes done, also where its
+    tasks wait for the sorted samples only (the spread's lists of samples in a
+    few cells take far longer than a forward call): any stream may then capture
+    calls on the plan without kbn_check_error."""
+    from paper_2111_02912_amd import batch as KB
+    from paper_2111_02912_amd.nufft import KbNufft
+    print("capture behind a captured batch", flush=True)
+    dev = torch.device("cuda", 0)
+    N, M = (24, 30, 20), 1500000
+    plan = KbNufft(N, device=dev)
+    om = torch.from_numpy((0.3 * W.uniform_random(M, 3, seed=94)).astype(np.float32)).to(dev)
+    x = torch.from_numpy(W.complex_normal((1,) + N, 95)).to(dev)
+    y = torch.empty((1, 1, M), dtype=torch.complex64, device=dev)
+    plan.set_points(om)
+    want = plan.forward(x).clone()
+    plan.check_error()
+    torch.cuda.synchronize()
+    plan.set_points(om)
+    b = KB.KbnBatch([KB.Task(plan, KB.FORWARD, 1, 1, x, y)], nstreams=1)
+    b.capture()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        out = plan.forward(x)
+    for _ in range(3):
+        out.zero_()
+        y.zero_()
+        g.replay()
+        b.launch()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(y, want)
+        plan.forward(x)
+        torch.cuda.synchronize()
+    b.close()
