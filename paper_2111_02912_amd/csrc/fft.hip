@@ -11,7 +11,7 @@
 //     outputs (forward), or all K inputs in and only the N kept rows out
 //     (adjoint crop).
 //   last adjoint pass (last axis): inverse transform, crop to N, scaling
-//     factors and conj(coil map), summed over coils.
+//     factors and conj(coil map); several coils are summed afterwards.
 // Forward transforms use exp(-2 pi i k n / K), inverse ones exp(+...), both
 // unnormalised.  Twiddles come from a host FP64 table rounded to float.
 #include "kbn_internal.h"
@@ -332,51 +332,23 @@ k_last_adj(KbnLastAdjArgs a, KbnRadix rp, const float2 *__restrict__ tw, int nl)
     const int nlb = (int)min((int64_t)nl, a.nlines - line0);
     const int Nl = a.Nl;
     const float *deap_l = a.deap[a.D - 1];
-    float2 acc[MAXE];
-#pragma unroll
-    for (int k = 0; k < MAXE; ++k) acc[k] = make_float2(0.f, 0.f);
-    for (int c = 0; c < a.C; ++c) {
-        for (int e = threadIdx.x; e < nlb * L; e += KBN_BLOCK) {
-            const int li = e / L;
-            const int p = e - li * L;
-            const int64_t line = line0 + li;
-            const int64_t bl = line / a.R0;
-            const int row = (int)(line - bl * a.R0);
-            buf[e] = a.in[(((bl * a.C + c) * a.R0) + row) * (int64_t)L + p];
-        }
-        __syncthreads();
-        fft_lds<MAXE, true>(buf, twl, rp, nl, L, 1, false);
-#pragma unroll
-        for (int k = 0; k < MAXE; ++k) {
-            const int e = threadIdx.x + k * KBN_BLOCK;
-            if (e < nlb * Nl) {
-                const int li = e / Nl;
-                const int j = e - li * Nl;
-                const int64_t line = line0 + li;
-                const int64_t bl = line / a.R0;
-                const int row = (int)(line - bl * a.R0);
-                float2 v = buf[li * L + wrap_pos(j, Nl, L)];
-                const int cm = a.cmod > 0 ? (int)(bl % a.cmod) : c;
-                if (a.smaps) v = cmulc(v, a.smaps[((int64_t)cm * a.R0 + row) * Nl + j]);
-                const float f = deap_l[j] * row_factor(row, a.D, a.N, a.deap, -1);
-                acc[k].x += v.x * f;
-                acc[k].y += v.y * f;
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int k = 0; k < MAXE; ++k) {
-        const int e = threadIdx.x + k * KBN_BLOCK;
-        if (e < nlb * Nl) {
-            float2 *dst = a.x + line0 * Nl + e;
-            if (a.accumulate) {
-                const float2 o = *dst;
-                *dst = make_float2(o.x + acc[k].x, o.y + acc[k].y);
-            } else {
-                *dst = acc[k];
-            }
-        }
+    for (int e = threadIdx.x; e < nlb * L; e += KBN_BLOCK) buf[e] = a.in[line0 * L + e];
+    __syncthreads();
+    fft_lds<MAXE, true>(buf, twl, rp, nl, L, 1, false);
+    for (int e = threadIdx.x; e < nlb * Nl; e += KBN_BLOCK) {
+        const int li = e / Nl;
+        const int j = e - li * Nl;
+        const int64_t line = line0 + li;
+        const int64_t bl = line / a.R0;
+        const int row = (int)(line - bl * a.R0);
+        float2 v = buf[li * L + wrap_pos(j, Nl, L)];
+        const int cm = a.cmod > 0 ? (int)(bl % a.cmod) : 0;
+        if (a.smaps) v = cmulc(v, a.smaps[((int64_t)cm * a.R0 + row) * Nl + j]);
+        const float f = deap_l[j] * row_factor(row, a.D, a.N, a.deap, -1);
+        v = make_float2(v.x * f, v.y * f);
+        float2 *dst = a.x + line0 * Nl + e;
+        if (a.accumulate) v = make_float2(dst->x + v.x, dst->y + v.y);
+        *dst = v;
     }
 }
 
@@ -431,7 +403,7 @@ hipError_t kbn_launch_mid_pass(const KbnMidPassArgs &a, const KbnRadix &rp, cons
     return hipGetLastError();
 }
 
-// coil sum of the per-coil images of the split last pass, in coil order
+// coil sum of the last pass's per-coil images, in coil order
 __global__ void __launch_bounds__(KBN_BLOCK)
 k_coil_sum(const float2 *__restrict__ ws, int64_t nb, int C, int64_t npix, float2 *__restrict__ x,
            int accumulate) {

@@ -449,8 +449,8 @@ __global__ void __launch_bounds__(256) k_any_first(KbnFirstPassArgs a, const flo
     });
 }
 
-// One coil a line (C = 1, with or without a map): each value is weighted and
-// stored as the last stage produces it.
+// One image or image-coil pair a line, with or without a map: each value is
+// weighted and stored as the last stage produces it.
 template <int L>
 __global__ void __launch_bounds__(256) k_any_last(KbnLastAdjArgs a, const float2 *__restrict__ tw) {
     using F = Any<L, true, 256, row_lines(L), false>;

@@ -7,9 +7,9 @@
 // Same operations as the runtime-length passes in fft.hip (forward first pass
 // with the scaling / coil / coordinate-weight prologue, strided forward and
 // inverse passes with zero-padding and cropping, last inverse pass with
-// crop, scaling and coil sum).  With L and the number E of elements per thread
-// known at compile time, every radix, stride and index is a constant.  Each thread holds the inputs of its E / R
-// butterflies in registers; stage 0 reads them straight from global memory
+// crop, scaling and coil map).  With L and the number E of elements per thread
+// known at compile time, every radix, stride and index is a constant.  Each
+// thread holds the inputs of its E / R butterflies in registers; stage 0 reads them straight from global memory
 // (zero-padding rows are never read), the last stage writes straight to
 // global memory (cropped rows are never written), and only the stages in
 // between exchange data through LDS.
@@ -546,8 +546,8 @@ __global__ void __launch_bounds__(NT) k_rows_first(KbnFirstPassArgs a, const flo
 }
 
 // ---- last inverse pass along the last axis (crop, scaling, coil map) -------
-// One coil a line (C = 1, with or without a map): each value is weighted and
-// stored as the last stage produces it.
+// One image or image-coil pair a line, with or without a map: each value is
+// weighted and stored as the last stage produces it.
 template <int L, int E, int NT>
 __global__ void __launch_bounds__(NT) k_rows_last_adj(KbnLastAdjArgs a, const float2 *__restrict__ tw) {
     using F = Fft<L, E, true>;

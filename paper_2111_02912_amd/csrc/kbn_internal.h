@@ -177,14 +177,14 @@ struct KbnMidPassArgs {        // FFT along a non-last axis, strided
     int dnw = 1;
 };
 
-struct KbnLastAdjArgs {        // adjoint: IFFT along the last axis + crop + scale + coil sum
-    const float2 *in;          // [nb*C][R0][L]
+struct KbnLastAdjArgs {        // adjoint: IFFT along the last axis + crop + scale + coil map
+    const float2 *in;          // [n][R0][L], n images or image-coil pairs
     const float2 *smaps;       // [C][R0][Nl] or null
-    float2 *x;                 // [nb][R0][Nl] (batch offset applied)
-    int64_t nlines;            // nb * R0
-    int R0, Nl, C;
-    int cmod;                  // > 0: C = 1 and line block bl takes coil map bl % cmod (one
-                               // output image per image-coil pair, summed afterwards)
+    float2 *x;                 // [n][R0][Nl]
+    int64_t nlines;            // n * R0
+    int R0, Nl;
+    int cmod;                  // > 0: in and x hold image-coil pairs (summed afterwards), pair
+                               // i takes coil map i % cmod; 0: images, all of coil map 0
     int accumulate;
     int D;
     int N[KBN_MAX_D];

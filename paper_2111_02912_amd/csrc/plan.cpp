@@ -762,7 +762,6 @@ int t1_passes(kbn_plan p, int64_t b0, int c0, int64_t nb, int ncc, const float2 
     la.nlines = split ? nb * ncc * R0 : nb * R0;
     la.R0 = (int)R0;
     la.Nl = Nl;
-    la.C = 1;
     la.cmod = split ? ncc : 0;
     la.accumulate = (!split && c0 > 0) ? 1 : 0;  // later coil runs add to the image
     la.D = D;
