@@ -20,6 +20,10 @@ int main(int, char **v) {
         std::printf("%lld", (long long)p);
         for (int x = 0; x < p; ++x) std::printf(" %d", kbn_xcd_run_index(x, (int)p));
     }
+    if (!std::strcmp(v[1], "xcdrow")) {  // n, row: the subproblem of each workgroup of that row
+        const int64_t p = kbn_xcd_padded(std::atoll(v[2]));
+        for (int x = 0; x < p; ++x) std::printf(" %d", kbn_xcd_run_index(x, (int)p, std::atoi(v[3])));
+    }
     if (!std::strcmp(v[1], "gather")) {  // D J M channels weights K.. T..: staged, blocks, channels per group, groups
         KbnGeom g = {};
         g.D = std::atoi(v[2]);
@@ -63,6 +67,18 @@ def test_gather_rows_hold_every_subproblem_once(rules, n):
     padded, *index = rules("xcd", n)
     assert padded % 8 == 0 and n <= padded < n + 8
     assert sorted(index) == list(range(padded))
+
+
+@pytest.mark.parametrize("n", [1, 5, 8, 17, 64, 70, 385])
+def test_gather_rows_take_turns_on_the_xcds(rules, n):
+    """Eight rows (channel groups) give every XCD, the workgroup's position modulo
+    eight, the same subproblems, of which the last may not exist."""
+    rows = [rules("xcdrow", n, r) for r in range(8)]
+    for r in rows:
+        assert sorted(r) == list(range(len(r)))
+    per_xcd = [sorted(s for r in rows for s in r[x::8]) for x in range(8)]
+    assert all(p == per_xcd[0] for p in per_xcd)
+    assert rules("xcdrow", n, 65535 * 8) == rows[0]
 
 
 @pytest.mark.parametrize("nch", [1, 2, 3, 7, 13])
