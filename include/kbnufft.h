@@ -243,8 +243,8 @@ int kbn_jac_omega_fwd(kbn_plan p, int B, int C, const void *x, const void *smaps
  * per image-coil pair than the two separate calls.  y equals kbn_forward's
  * bit for bit; domega agrees with kbn_jac_omega_fwd to float32 rounding
  * (the r^[0] scaling is applied after the first pass instead of before).
- * Other dimensions, and grids with an edge below 128 (launch-bound), run
- * the two calls.  x: c64 [B][N...];
+ * Other dimensions, and grids with an edge below 128, run the two calls, so
+ * that domega has the bits of kbn_jac_omega_fwd there.  x: c64 [B][N...];
  * y, g: c64 [B][C][M] (y and g must not overlap); domega: device float32
  * [M][D]; accumulate = 0 overwrites domega, 1 adds.  The workspace holds
  * D + 1 grids per image-coil pair (kbn_plan_footprint does not count it).

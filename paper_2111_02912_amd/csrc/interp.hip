@@ -1230,22 +1230,43 @@ k_reduce_parts(float *__restrict__ dst, const float *__restrict__ part, int64_t 
 
 }  // namespace
 
-// Channel groups of a gather over `blocks` point blocks and nbc image-coil
-// pairs.  At least the KBN_GATHER_WG_MIN workgroups that fill the GPU; beyond
-// that KBN_GATHER_WG_TARGET of them, whose durations differ with the points they
-// hold, so that several rounds even out (five are resident per CU), but only
-// while a group keeps KBN_GATHER_PAIRS pairs: every group repeats the points'
-// weights, and an omega-Jacobian writes and sums one partial gradient per group.
-// Forward and omega-Jacobian of 256^2 x 256 channels: target 2048 177 and 285 us,
-// 4096 161 and 262, 8192 157 and 249, more the same.  The target without the
-// bound on pairs against with it, whole omega-Jacobian calls: 48^2 x 400 121 and 99
-// us, 64^2 x 64 56 and 48, 192^2 x 32 94 and 85, 256^2 x 2 with M = 2M 154 and 127,
-// 75 x 90 x 64 x 4 534 and 515; forward 180 and 166 there, but 27 x 27 x 35 x 24
-// (sigma 1.25) 85 and 92 (two pairs kept 85, and 40^3 x 32 then 193 instead of 187).
-int64_t kbn_gather_groups(int64_t blocks, int64_t nbc) {
+// Channel groups of a gather over `blocks` point blocks and nbc image-coil pairs.
+//
+// Staged: at least the KBN_GATHER_WG_MIN workgroups that fill the GPU; beyond that
+// KBN_GATHER_WG_TARGET of them, whose durations differ with the points they hold,
+// so that several rounds even out (five are resident per CU), but only while a
+// group keeps KBN_GATHER_PAIRS pairs: every group repeats the points' weights, and
+// an omega-Jacobian writes and sums one partial gradient per group.  Forward and
+// omega-Jacobian of 256^2 x 256 channels: target 2048 177 and 285 us, 4096 161 and
+// 262, 8192 157 and 249, more the same.  Pairs kept, whole calls (us), 1 / 2 / 4: 256^2
+// x 2 with M = 2M, omega-Jacobian 153 / 128 / 127; 64^2 x 64 38.4 / 36.0 / 36.0; 239 x
+// 137 x 16 forward 55.8 / 55.6 / 58.1; 20^3 x 64 omega-Jacobian 144 / 144 / 151; 48^2 x
+// 400 78 / 77 / 81.
+//
+// Direct: KBN_GATHER_WG_ROUND workgroups are resident at once (four per CU) and each
+// evaluates its points' weights and tap indexes first, so either one round of
+// them, or so many that a round more or less does not matter.  One round / a
+// group per pair (us): 82 x 23 x 25 x 110, J = 8, forward 1115 / 1644, omega-Jacobian
+// 3425 / 5005; 105^3 x 4, J = 8, 1026 / 1283; 40^3 x 8, M = 96000 (three rounds), 614 /
+// 823.  From four rounds on a group per pair: 50^3 x 8, J = 8, omega-Jacobian 6445
+// against 8523 in one round; 40^3 x 12, M = 96000, even.
+int64_t kbn_gather_groups(int64_t blocks, int64_t nbc, bool staged) {
+    if (!staged) {
+        if (blocks * nbc <= KBN_GATHER_WG_ROUND) return std::max<int64_t>(1, nbc);
+        if (blocks * nbc < 4 * KBN_GATHER_WG_ROUND && blocks <= KBN_GATHER_WG_ROUND)
+            return KBN_GATHER_WG_ROUND / blocks;
+        return kbn_gather_groups_most(blocks, nbc, staged);
+    }
     const int64_t fill = (KBN_GATHER_WG_MIN + blocks - 1) / blocks;
     const int64_t even = std::min((KBN_GATHER_WG_TARGET + blocks - 1) / blocks, nbc / KBN_GATHER_PAIRS);
     return std::max<int64_t>(1, std::min<int64_t>(nbc, std::max(fill, even)));
+}
+
+// The most groups that kbn_gather_groups gives nbc pairs or fewer (its count never
+// falls with nbc in the staged form, in the direct one it may).
+int64_t kbn_gather_groups_most(int64_t blocks, int64_t nbc, bool staged) {
+    if (staged) return kbn_gather_groups(blocks, nbc, staged);
+    return std::max<int64_t>(1, std::min<int64_t>(nbc, (KBN_GATHER_WG_TARGET + blocks - 1) / blocks));
 }
 
 // Launch shape of the gather: staged (LDS region fits 48 KiB) or direct, and
@@ -1266,9 +1287,9 @@ KbnGatherShape kbn_gather_shape(const KbnGeom &g, int64_t M, int nch, int nw) {
     if (sh.staged)
         blocks = (M + KBN_SUB - 1) / KBN_SUB + g.ntiles + 1;
     else
-        blocks = (M + KBN_BLOCK - 1) / KBN_BLOCK;
+        blocks = std::max<int64_t>(1, (M + KBN_BLOCK - 1) / KBN_BLOCK);
     sh.blocks = blocks;
-    const int64_t groups = kbn_gather_groups(blocks, nbc);
+    const int64_t groups = kbn_gather_groups(blocks, nbc, sh.staged);
     sh.cg = (int)(((nbc + groups - 1) / groups) * nw);
     // the staged gather's whole channel pairs (8 channels one by one 21 us, in
     // pairs 16 us); the direct one takes a channel at a time (40 x 48 x 36 x 2,

@@ -20,7 +20,8 @@
 #define KBN_SUB 256        // sorted points per gather subproblem (one per thread)
 #define KBN_GATHER_WG_MIN 2048     // workgroups (point blocks x channel groups) that fill the GPU
 #define KBN_GATHER_WG_TARGET 8192  // workgroups a gather aims for while its groups keep
-#define KBN_GATHER_PAIRS 4         // this many image-coil pairs
+#define KBN_GATHER_PAIRS 2         // this many image-coil pairs
+#define KBN_GATHER_WG_ROUND 1024   // workgroups of the direct gather resident at once
 #define KBN_SPREAD_EB 64   // list entries staged per spread batch
 #define KBN_SPREAD_SEG 128  // list entries per spread work item (doubled if slots run out)
 #define KBN_SPREAD_SMAX 256 // partial-tile slots for tiles split into several work items
@@ -252,10 +253,11 @@ struct KbnGatherShape {
     int64_t blocks;
     int cg, groups;
 };
-// Nominal channel groups of a gather over nbc channel sets in `blocks`
-// point blocks: never more than nbc, and never fewer for a larger nbc, so
-// that it bounds the groups of every smaller chunk as well.
-int64_t kbn_gather_groups(int64_t blocks, int64_t nbc);
+// Channel groups of a gather over nbc channel sets in `blocks` point blocks (at
+// most nbc), and the most of any number of sets up to nbc: the workspace of a
+// call's largest chunk has to hold every smaller one's.
+int64_t kbn_gather_groups(int64_t blocks, int64_t nbc, bool staged);
+int64_t kbn_gather_groups_most(int64_t blocks, int64_t nbc, bool staged);
 KbnGatherShape kbn_gather_shape(const KbnGeom &g, int64_t M, int nch, int nw);
 
 struct KbnSpreadArgs {

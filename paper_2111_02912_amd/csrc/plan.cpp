@@ -483,17 +483,15 @@ static Chunks split_chunks(int64_t B, int C, int64_t per_coil, int64_t max_ws) {
 // most `units` image-coil pairs (nw = D weighted channels each).
 int64_t jac_part_bytes(const kbn_plan p, int64_t M, int64_t units) {
     const int nw = p->D;
-    const int64_t blocks0 = kbn_gather_shape(p->geom(), M, (int)(units * nw), nw).blocks;
-    const int64_t groups_max = kbn_gather_groups(blocks0, units);
-    return groups_max * M * p->D * (int64_t)sizeof(float);
+    const KbnGatherShape sh = kbn_gather_shape(p->geom(), M, (int)(units * nw), nw);
+    return kbn_gather_groups_most(sh.blocks, units, sh.staged) * M * p->D * (int64_t)sizeof(float);
 }
 
 // Grid workspace of one call (bytes), the larger chunk's share under the
 // workspace cap.  Type 2 (forward, nw weight channels per coil; mode 1 adds
 // the per-group partial omega-gradients: the gather's point blocks do not
-// depend on the channel count, and a chunk's channel groups are at most
-// kbn_gather_groups of its image-coil pairs, a bound that also holds for
-// every smaller chunk).
+// depend on the channel count, and kbn_gather_groups_most bounds the channel
+// groups of a chunk and of every smaller one).
 int64_t ws_type2(const kbn_plan p, int64_t M, int B, int C, int nw, int mode) {
     const int64_t per_coil = (int64_t)nw * p->gsize() * (int64_t)sizeof(float2) * 2;
     const Chunks ck = split_chunks(B, C, per_coil, p->max_ws);
@@ -716,7 +714,8 @@ KbnSpreadArgs t1_spread_args(kbn_plan p, int64_t nch, const float2 *y_chunk, flo
     sa.rec_t = p->rec_t;
     sa.nwork_max = (int)p->swork_cap;
     // (a list of at most SEG entries is not split, and a tile lists a sample once:
-    // one launch fewer, 40^2 Gram layer with 80 samples 292 -> 284 us)
+    // one launch fewer, the adjoint of 40^2 x 8 coils 23 us with 128 samples and 26
+    // with 129)
     sa.ncomb_max = p->M <= KBN_SPREAD_SEG ? 0 : std::min<int>(p->ntiles_own, spread_slots(p, p->M) / 2);
     return sa;
 }
@@ -823,15 +822,18 @@ int run_jac(kbn_plan p, int B, int C, const float2 *img, const float2 *smaps, co
 }
 
 // y = E x and the omega-gradient of run_jac in one pass.  In 2D with grid
-// edges of at least 128 (below, the passes are launch-bound), the first pass (along axis 1) transforms the
+// edges of at least 128, the first pass (along axis 1) transforms the
 // unweighted and the r^[1]-weighted images only: r^[0] is constant along
 // axis-1 lines, so the axis-0 pass derives the r^[0] channel by scaling the
 // unweighted channel's rows (the persistent pass scales the values it holds
-// for the source tile).  This saves one grid-row write and one read per image-coil pair
-// against kbn_forward followed by kbn_jac_omega_fwd.  The unweighted channel
-// goes through the same steps as in kbn_forward (same y bits); the derived
-// channel rounds the product r^[0] * window scale in another order than
-// the weighted first pass.  Other shapes run the two calls.
+// for the source tile).  This saves one grid-row write and one read per
+// image-coil pair against kbn_forward followed by kbn_jac_omega_fwd.  The
+// unweighted channel goes through the same steps as in kbn_forward (same y
+// bits); the derived channel rounds the product r^[0] * window scale in another
+// order than the weighted first pass.  Other shapes run the two calls: 1D has no
+// second axis, 3D is not built, and smaller 2D grids, where one call is faster
+// too (us against two: 40^2 26.6 and 31.5, 63^2 x 256 98 and 114), keep
+// kbn_jac_omega_fwd's bits, which this call has always given them.
 int run_fwd_jac(kbn_plan p, int B, int C, const float2 *x, const float2 *smaps, float2 *y, const float2 *g,
                 float *dom, int accumulate, hipStream_t stream) {
     const int D = p->D;

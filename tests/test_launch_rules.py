@@ -38,6 +38,16 @@ int main(int, char **v) {
         const KbnGatherShape sh = kbn_gather_shape(g, std::atoll(v[4]), std::atoi(v[5]), std::atoi(v[6]));
         std::printf("%d %d %d %d", (int)sh.staged, (int)sh.blocks, sh.cg, sh.groups);
     }
+    if (!std::strcmp(v[1], "most")) {  // blocks, pairs: 0 if the groups of every smaller number of pairs fit
+        const int64_t b = std::atoll(v[2]), n = std::atoll(v[3]);
+        int bad = 0;
+        for (int staged = 0; staged < 2; ++staged)
+            for (int64_t k = 1; k <= n; ++k) {
+                const int64_t g = kbn_gather_groups(b, k, staged);
+                bad += g < 1 || g > k || g > kbn_gather_groups_most(b, n, staged);
+            }
+        std::printf("%d", bad);
+    }
     if (!std::strcmp(v[1], "counts"))  // sort tiles, owner tiles, M..: integers of the index pass
         for (int i = 4; v[i]; ++i)
             std::printf("%lld ", (long long)kbn_points_counts_size(std::atoll(v[i]), std::atoi(v[2]), std::atoi(v[3])));
@@ -81,12 +91,26 @@ def test_gather_rows_take_turns_on_the_xcds(rules, n):
     assert rules("xcdrow", n, 65535 * 8) == rows[0]
 
 
-@pytest.mark.parametrize("nch", [1, 2, 3, 7, 13])
-def test_direct_gather_takes_channels_one_by_one(rules, nch):
-    """Few point blocks without an LDS region: a workgroup row per channel."""
+@pytest.mark.parametrize("nch", [1, 2, 3, 6, 7, 13, 20, 26, 27, 60, 200])
+def test_direct_gather_takes_one_round_of_workgroups_or_many(rules, nch):
+    """Point blocks without an LDS region: a workgroup row per channel, unless that
+    is between one and four rounds of resident workgroups."""
     staged, blocks, cg, groups = rules("gather", 3, 8, 40000, nch, 1, 80, 96, 72, 8, 8, 8)
-    assert not staged and blocks * nch < 2048 + blocks  # not more than fill the GPU
-    assert cg == 1 and groups == nch
+    assert not staged and blocks == 157
+    if blocks * nch <= 1024:
+        assert cg == 1 and groups == nch
+    elif blocks * nch < 4096:
+        assert cg > 1 and blocks * groups <= 1024
+    else:
+        assert blocks * groups > 4096 or groups == nch
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 8, 100, 157, 512, 1023, 1024, 1025, 3000, 8191, 8192, 20000])
+@pytest.mark.parametrize("nbc", [1, 2, 7, 64, 1000, 9000])
+def test_workspace_holds_the_groups_of_every_smaller_chunk(rules, blocks, nbc):
+    """An omega-Jacobian keeps one partial gradient per channel group in a
+    workspace sized by the largest chunk of a call."""
+    assert rules("most", blocks, nbc) == [0]
 
 
 # (M, image-coil pairs, weights, K, T): one wave of subproblems and many, few
@@ -100,7 +124,7 @@ def test_gather_groups_keep_pairs_once_the_gpu_is_filled(rules, M, nbc, nw, K, T
     staged, blocks, cg, groups = rules("gather", len(K), 6, M, nbc * nw, nw, *K, *T)
     assert cg % nw == 0 and (groups - 1) * cg < nbc * nw <= groups * cg
     fill = -(-2048 // blocks)  # groups that fill the GPU
-    assert groups <= fill or cg // nw >= 4
+    assert groups <= fill or cg // nw >= 2
     if nbc >= 4 * 32:  # many pairs: several rounds of workgroups
         assert blocks * groups >= min(8192, blocks * nbc // 8)
 
