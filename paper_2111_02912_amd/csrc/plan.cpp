@@ -1165,12 +1165,13 @@ int plan_setup(kbn_plan p, int D, const int64_t *N, const kbn_opts *opts) {
     p->ntiles = (int)ntiles;
     // spread owner tiles: even splits of each axis near the preferred edge, at
     // least J - 1 wide so that a J-tap footprint meets at most two per axis.  More
-    // than KBN_MAX_TILES of them only where the matrix-core spread takes them and
-    // the preferred edge is its 8 cells already: smaller tiles fill its operands
-    // less (96^3, J = 4, one channel: 4-cell tiles 319 us, 8-cell 132), and the other
-    // spreads then do better with larger ones.
+    // than KBN_MAX_TILES of them only where the matrix-core spread takes them; the
+    // other spreads then do better with larger ones.  In 2D and 3D no preferred edge
+    // below that spread's 8 cells: its operands hold 8 x 8 cells whatever the tile (us,
+    // 4- / 8-cell tiles, J = 4: 64^3, 20000 samples 115 / 42; 96^3, 100000 319 / 132; 128^2 x
+    // 256, 60000 795 / 528; 128^2 x 8 33 / 29).
     int64_t ntiles_own = 1;
-    int defown = o.spread_tile > 0 ? std::max(J, o.spread_tile) : (D == 1 ? 128 : 8);
+    int defown = D == 1 ? (o.spread_tile > 0 ? std::max(J, o.spread_tile) : 128) : std::max(8, o.spread_tile);
     for (;;) {
         ntiles_own = 1;
         int most = 1;
@@ -1184,8 +1185,8 @@ int plan_setup(kbn_plan p, int D, const int64_t *N, const kbn_opts *opts) {
             most = std::max(most, p->To[d]);
         }
         if (ntiles_own <= KBN_MAX_TILES || defown >= KBN_MAX_K) break;
-        if (D >= 2 && most <= 8 && defown >= 8 && ntiles_own <= KBN_MAX_OWN) break;
-        defown = defown < 8 ? 8 : defown + 4;
+        if (D >= 2 && most <= 8 && ntiles_own <= KBN_MAX_OWN) break;
+        defown += 4;
     }
     if (ntiles_own > KBN_MAX_OWN) {
         return fail(KBN_ERR_UNSUPPORTED, "too many spread tiles");

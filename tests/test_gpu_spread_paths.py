@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 def _edges(K, J, spread_tile):
     """Largest owner tile edge per axis."""
-    want = max(J, spread_tile) if spread_tile else (128 if len(K) == 1 else 8)
+    want = (max(J, spread_tile) if spread_tile else 128) if len(K) == 1 else max(8, spread_tile)
     out = []
     for k in K:
         n = -(-k // want)
