@@ -823,9 +823,11 @@ __device__ __forceinline__ void lane_coefs(const float *__restrict__ coef, float
 
 // 2D: a workgroup of four waves per (work item, 32 / CS * NG channels).  CS
 // waves share the tile's four 2-row blocks and 4 / CS take different
-// channels, 8 * NG each.
+// channels, 8 * NG each.  The values come from the caller's array, or (grouped)
+// from the copy in tile order with a group's channels side by side.
 template <int J, int CS, int NG>
-__global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5) k_spread_mf2(KbnGeom g, KbnSpreadArgs a) {
+__global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5)
+k_spread_mf2(KbnGeom g, KbnSpreadArgs a, bool grouped) {
     constexpr int CHW = 32 / CS * NG;                          // channels per workgroup
     constexpr int BW = 4 / CS;                                 // blocks per wave
     constexpr int EB = CHW <= 8 ? 64 : (CHW <= 32 ? 32 : 16);  // entries per batch
@@ -845,12 +847,17 @@ __global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5) k_spread_mf2(KbnGeom
     // staging: weights of (entry te + 16 pass, axis ax, cell cc), values of
     // (entry ty, channels kb + 256 / EB r)
     const int te = tid >> 4, ax = (tid >> 3) & 1, cc = tid & 7;
-    const int ty = tid % EB, kb = tid / EB;
+    const int ty = grouped ? tid / (256 / EB) : tid % EB, kb = grouped ? tid % (256 / EB) : tid / EB;
     const int Kx = ax ? g.K[1] : g.K[0];
     const int wpos = ax ? 8 + cc : (cc & 1) * 4 + (cc >> 1);
     const float2 *yb[YF];
 #pragma unroll
-    for (int r = 0; r < YF; ++r) yb[r] = a.y + (int64_t)(ch0 + min(kb + 256 / EB * r, nchg - 1)) * a.M;
+    for (int r = 0; r < YF; ++r) {
+        const int c = min(kb + 256 / EB * r, nchg - 1);
+        yb[r] = grouped ? a.ys + (int64_t)ch0 * a.M + c : a.y + (int64_t)(ch0 + c) * a.M;
+    }
+    const int *rec_y = grouped ? a.rec_p : a.rec_q;
+    const int ystep = grouped ? nchg : 1;
     const int nwork = a.scounts[0];
     int wk = blockIdx.y;
     int4 item = reinterpret_cast<const int4 *>(a.swork)[wk];  // tile, first entry, end, slot
@@ -860,11 +867,11 @@ __global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5) k_spread_mf2(KbnGeom
     // loads of the n entries from eb on; lanes past them repeat the last one,
     // so that all loads are issued without branches (stage writes zeros there)
     auto index = [&](int eb, int n) {
-        if (n > 0) q = a.rec_q[eb + min(ty, n - 1)];
+        if (n > 0) q = rec_y[eb + min(ty, n - 1)];
     };
     auto fetch = [&](int eb, int n) {
 #pragma unroll
-        for (int r = 0; r < YF; ++r) yv[r] = yb[r][q];
+        for (int r = 0; r < YF; ++r) yv[r] = yb[r][(int64_t)q * ystep];
         const int2 *tb = a.rec_t + 2 * (int64_t)eb + ax;
 #pragma unroll
         for (int p = 0; p < TP; ++p) t[p] = tb[2 * min(te + 16 * p, n - 1)];
@@ -1427,18 +1434,18 @@ hipError_t launch_os_multi(const KbnSpreadSel &sel, dim3 grid, const KbnSpreadJo
 template <int D, int J>
 hipError_t launch_mf(const KbnSpreadSel &sel, const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)sel.ngr, (unsigned)sel.ny);
+    if (sel.grouped) {
+        const dim3 pgrid((unsigned)((a.M * sel.cpt + KBN_BLOCK - 1) / KBN_BLOCK), (unsigned)sel.ngr);
+        k_permute_groups<<<pgrid, dim3(KBN_BLOCK), 0, s>>>(a.y, a.ys, a.order, a.M, a.nch, sel.cpt);
+    }
     if constexpr (D == 2) {
         switch (sel.cpt) {
-            case 8: k_spread_mf2<J, 4, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
-            case 16: k_spread_mf2<J, 2, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
-            case 32: k_spread_mf2<J, 1, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
-            default: k_spread_mf2<J, 1, 2><<<grid, dim3(256), 0, s>>>(g, a); break;
+            case 8: k_spread_mf2<J, 4, 1><<<grid, dim3(256), 0, s>>>(g, a, sel.grouped); break;
+            case 16: k_spread_mf2<J, 2, 1><<<grid, dim3(256), 0, s>>>(g, a, sel.grouped); break;
+            case 32: k_spread_mf2<J, 1, 1><<<grid, dim3(256), 0, s>>>(g, a, sel.grouped); break;
+            default: k_spread_mf2<J, 1, 2><<<grid, dim3(256), 0, s>>>(g, a, sel.grouped); break;
         }
     } else {
-        if (a.M > 0) {
-            const dim3 pgrid((unsigned)((a.M * sel.cpt + KBN_BLOCK - 1) / KBN_BLOCK), (unsigned)sel.ngr);
-            k_permute_groups<<<pgrid, dim3(KBN_BLOCK), 0, s>>>(a.y, a.ys, a.order, a.M, a.nch, sel.cpt);
-        }
         switch (sel.cpt) {
             case 8: k_spread_mf3<J, 1, 1><<<grid, dim3(512), 0, s>>>(g, a); break;
             case 4: k_spread_mf3<J, 2, 1><<<grid, dim3(256), 0, s>>>(g, a); break;
@@ -1567,6 +1574,16 @@ KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a) {
             sel.cpt = a.nch <= 1 ? 1 : (a.nch <= 2 ? 2 : (a.nch <= 4 ? 4 : 8));
         sel.ngr = (a.nch + sel.cpt - 1) / sel.cpt;
         sel.ny = std::min(a.nwork_max, KBN_GRID_Y_MAX);
+        // The values in tile order first: always in 3D, where eight tiles may read a
+        // sample's, and in 2D where it was measured to pay (whole adjoints, us,
+        // straight / grouped): 128^2 x 128, 60000 samples 326 / 229 (radial 345 / 233;
+        // J = 4 266 / 217; by the cell-per-thread kernel 271), 16000 103 / 88; 256^2 x 256,
+        // 32768 663 / 607.  Not for values that fit the L2s (2^20 of them are 8 MB; 150 x
+        // 90 x 48, 5000 samples 40.5 / 43.5), for few tiles (64^2 x 64, 60000, J = 4 87 /
+        // 103), fewer than four samples a tile (320^2 x 128, 20480, J = 4 414 / 427) or
+        // up to 32 channels (64^2 x 32, 60000 62 / 68, though 256^2 x 32, 120000 202 / 142)
+        sel.grouped = a.M > 0 && (D == 3 || (a.nch > 32 && (int64_t)a.nch * g.ntiles_own >= 32768 &&
+                                             a.M >= 4 * (int64_t)g.ntiles_own && a.M * a.nch >= 1 << 20));
         return sel;
     }
     if (D == 2 && tcells <= 512 && os_on) {

@@ -310,6 +310,7 @@ struct KbnSpreadSel {
     int cpt = 0;             // channels per thread (output-stationary) or per workgroup (matrix-core)
     int tcells = 0;          // cells of an owner tile
     int ngr = 0, ny = 0;     // grid: channel groups x work-item rows
+    bool grouped = false;    // matrix-core: values copied in tile order, a group's channels side by side
 };
 KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a);
 struct KbnSpreadJob {

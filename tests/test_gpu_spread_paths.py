@@ -87,6 +87,33 @@ def test_matrix_core_spread_of_eight_taps(N, M, nch):
         assert np.array_equal(got[c:c + 1], _adjoint(p, y[c:c + 1]))
 
 
+# many values on many tiles: copied in tile order first, from 2^20 of them, 4 samples a
+# tile (800 tiles of 256 x 200) and 32768 (tile, channel) pairs on; groups of 64
+# channels and a remainder
+@pytest.mark.parametrize("M,nch", [(25575, 41), (25576, 41), (26300, 40), (16383, 64), (16384, 64), (16384, 65),
+                                   (8100, 130), (3199, 330), (3200, 330)])
+def test_matrix_core_spread_of_many_channels(M, nch):
+    from paper_2111_02912_amd.cg import cg_sense
+    N = (128, 100)
+    print(f"2D spread of {nch} channels, M={M}", flush=True)
+    om = _samples(M, 2)
+    om[7::11, 0] = np.nan
+    y = W.complex_normal((nch, 1, M), 67)
+    p = _plan(N, om, "matrix")
+    got = _adjoint(p, y)
+    q = _plan(N, om, "scatter", 6, 32)
+    ref = _adjoint(q, y)
+    assert np.isfinite(got).all() and np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+    ok = np.isfinite(om).all(1)
+    pix = np.sort(W.rng(68).choice(int(np.prod(N)), 300, replace=False))
+    want = ndft.adjoint(om[ok], np.ascontiguousarray(y[:, 0, ok]), N, pix=pix)
+    assert ndft.rel_l2(got.reshape(nch, -1)[:, pix], want) < 2e-5
+    x = cg_sense(p, torch.from_numpy(y).to(p.device), None, lam=float(M), iters=2)[0]  # E p in tile order
+    for c in {0, 31, nch - 1}:
+        assert np.array_equal(got[c:c + 1], _adjoint(p, y[c:c + 1]))
+        assert torch.equal(x[c:c + 1], cg_sense(p, torch.from_numpy(y[c:c + 1]).to(p.device), None, lam=float(M), iters=2)[0])
+
+
 def test_cg_and_jacobian_through_the_2d_scatter_kernel():
     """Flagged samples stay out of a solve, whose E p is in tile order, and the
     adjoint operator with coil maps and its Jacobian match the NUDFT."""
