@@ -1578,12 +1578,15 @@ KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a) {
         // sample's, and in 2D where it was measured to pay (whole adjoints, us,
         // straight / grouped): 128^2 x 128, 60000 samples 326 / 229 (radial 345 / 233;
         // J = 4 266 / 217; by the cell-per-thread kernel 271), 16000 103 / 88; 256^2 x 256,
-        // 32768 663 / 607.  Not for values that fit the L2s (2^20 of them are 8 MB; 150 x
-        // 90 x 48, 5000 samples 40.5 / 43.5), for few tiles (64^2 x 64, 60000, J = 4 87 /
-        // 103), fewer than four samples a tile (320^2 x 128, 20480, J = 4 414 / 427) or
-        // up to 32 channels (64^2 x 32, 60000 62 / 68, though 256^2 x 32, 120000 202 / 142)
-        sel.grouped = a.M > 0 && (D == 3 || (a.nch > 32 && (int64_t)a.nch * g.ntiles_own >= 32768 &&
-                                             a.M >= 4 * (int64_t)g.ntiles_own && a.M * a.nch >= 1 << 20));
+        // 32768 663 / 607; 62^2 x 300, 5000 94 / 72.  Not for values that fit the L2s (2^20
+        // of them are 8 MB; 150 x 90 x 48, 5000 samples 40.5 / 43.5), or on few tiles the
+        // Infinity Cache's share (2^22; 28^2 x 744, 2767 61 / 72, 20000 538 / 279; 64^2 x 64,
+        // 60000, J = 4 87 / 103; 56^2 x 300, 30000 399 / 209), for fewer than four samples a
+        // tile (320^2 x 128, 20480, J = 4 414 / 427) or up to 32 channels (64^2 x 32, 60000 62
+        // / 68, though 256^2 x 32, 120000 202 / 142)
+        const int64_t vals = a.M * a.nch, tiles = g.ntiles_own;
+        const bool many = tiles >= 256 && a.nch * tiles >= 32768 ? vals >= 1 << 20 : tiles >= 25 && vals >= 1 << 22;
+        sel.grouped = a.M > 0 && (D == 3 || (a.nch > 32 && a.M >= 4 * tiles && many));
         return sel;
     }
     if (D == 2 && tcells <= 512 && os_on) {
