@@ -823,11 +823,12 @@ __device__ __forceinline__ void lane_coefs(const float *__restrict__ coef, float
 
 // 2D: a workgroup of four waves per (work item, 32 / CS * NG channels).  CS
 // waves share the tile's four 2-row blocks and 4 / CS take different
-// channels, 8 * NG each.  The values come from the caller's array, or (grouped)
-// from the copy in tile order with a group's channels side by side.
+// channels, 8 * NG each.  The values come from the caller's array, or (grouped,
+// samples not along a trajectory) from the copy in tile order with a group's
+// channels side by side.
 template <int J, int CS, int NG>
 __global__ void __launch_bounds__(256, CS * NG > 2 ? 6 : 5)
-k_spread_mf2(KbnGeom g, KbnSpreadArgs a, bool grouped) {
+k_spread_mf2(KbnGeom g, KbnSpreadArgs a, bool may_group) {  // (NG = 2 only)
     constexpr int CHW = 32 / CS * NG;                          // channels per workgroup
     constexpr int BW = 4 / CS;                                 // blocks per wave
     constexpr int EB = CHW <= 8 ? 64 : (CHW <= 32 ? 32 : 16);  // entries per batch
@@ -847,6 +848,7 @@ k_spread_mf2(KbnGeom g, KbnSpreadArgs a, bool grouped) {
     // staging: weights of (entry te + 16 pass, axis ax, cell cc), values of
     // (entry ty, channels kb + 256 / EB r)
     const int te = tid >> 4, ax = (tid >> 3) & 1, cc = tid & 7;
+    const bool grouped = NG == 2 && may_group && a.scounts[2] == 0;
     const int ty = grouped ? tid / (256 / EB) : tid % EB, kb = grouped ? tid % (256 / EB) : tid / EB;
     const int Kx = ax ? g.K[1] : g.K[0];
     const int wpos = ax ? 8 + cc : (cc & 1) * 4 + (cc >> 1);
@@ -961,17 +963,19 @@ k_spread_mf2(KbnGeom g, KbnSpreadArgs a, bool grouped) {
 
 // k-space of each group of `cg` channels in tile order with the group's
 // channels side by side, so that one entry's values are one short read:
-// ys[group * cg * M + p * width + c] (width = channels of the group).
+// ys[group * cg * M + p * width + c] (width = channels of the group).  Nothing to do
+// where *along (if given) says that the samples come along a trajectory.
 __global__ void __launch_bounds__(KBN_BLOCK)
 k_permute_groups(const float2 *__restrict__ y, float2 *__restrict__ ys, const int *__restrict__ order, int64_t M,
-                 int nch, int cg) {
+                 int nch, int cg, const int *__restrict__ along) {
+    if (along && *along) return;
     const int ch0 = blockIdx.y * cg;
     const int w = min(cg, nch - ch0);
-    const int64_t i = (int64_t)blockIdx.x * KBN_BLOCK + threadIdx.x;
-    const int64_t p = i / w;
-    if (p >= M) return;
-    const int c = (int)(i - p * w);
-    ys[(int64_t)ch0 * M + i] = y[(int64_t)(ch0 + c) * M + sample_index(order, p)];
+    for (int64_t i = (int64_t)blockIdx.x * KBN_BLOCK + threadIdx.x; i < M * w; i += (int64_t)gridDim.x * KBN_BLOCK) {
+        const int64_t p = i / w;
+        const int c = (int)(i - p * w);
+        ys[(int64_t)ch0 * M + i] = y[(int64_t)(ch0 + c) * M + sample_index(order, p)];
+    }
 }
 
 // 3D: a workgroup of 8 / S * CS waves per (work item, 8 / S channels), each
@@ -1435,8 +1439,12 @@ template <int D, int J>
 hipError_t launch_mf(const KbnSpreadSel &sel, const KbnGeom &g, const KbnSpreadArgs &a, hipStream_t s) {
     const dim3 grid((unsigned)sel.ngr, (unsigned)sel.ny);
     if (sel.grouped) {
-        const dim3 pgrid((unsigned)((a.M * sel.cpt + KBN_BLOCK - 1) / KBN_BLOCK), (unsigned)sel.ngr);
-        k_permute_groups<<<pgrid, dim3(KBN_BLOCK), 0, s>>>(a.y, a.ys, a.order, a.M, a.nch, sel.cpt);
+        // 2D: a bounded grid, which ends at once where there is nothing to copy
+        const int64_t nb = (a.M * sel.cpt + KBN_BLOCK - 1) / KBN_BLOCK;
+        const int64_t most = D == 2 ? std::max(1, 8192 / sel.ngr) : nb;
+        const dim3 pgrid((unsigned)std::min(nb, most), (unsigned)sel.ngr);
+        k_permute_groups<<<pgrid, dim3(KBN_BLOCK), 0, s>>>(a.y, a.ys, a.order, a.M, a.nch, sel.cpt,
+                                                           D == 2 ? a.scounts + 2 : nullptr);
     }
     if constexpr (D == 2) {
         switch (sel.cpt) {
@@ -1575,18 +1583,20 @@ KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a) {
         sel.ngr = (a.nch + sel.cpt - 1) / sel.cpt;
         sel.ny = std::min(a.nwork_max, KBN_GRID_Y_MAX);
         // The values in tile order first: always in 3D, where eight tiles may read a
-        // sample's, and in 2D where it was measured to pay (whole adjoints, us,
-        // straight / grouped): 128^2 x 128, 60000 samples 326 / 229 (radial 345 / 233;
-        // J = 4 266 / 217; by the cell-per-thread kernel 271), 16000 103 / 88; 256^2 x 256,
-        // 32768 663 / 607; 62^2 x 300, 5000 94 / 72.  Not for values that fit the L2s (2^20
-        // of them are 8 MB; 150 x 90 x 48, 5000 samples 40.5 / 43.5), or on few tiles the
-        // Infinity Cache's share (2^22; 28^2 x 744, 2767 61 / 72, 20000 538 / 279; 64^2 x 64,
-        // 60000, J = 4 87 / 103; 56^2 x 300, 30000 399 / 209), for fewer than four samples a
-        // tile (320^2 x 128, 20480, J = 4 414 / 427) or up to 32 channels (64^2 x 32, 60000 62
-        // / 68, though 256^2 x 32, 120000 202 / 142)
+        // sample's, and in 2D where it was measured to pay, for samples in no order (whole
+        // adjoints, us, straight / grouped): 128^2 x 128, 60000 samples 326 / 229 (J = 4 266
+        // / 217; by the cell-per-thread kernel 271); 256^2 x 256, 32768 663 / 607; 256^2 x 64,
+        // 131072 460 / 314.  Along a trajectory the values of a tile share their lines
+        // (256^2 x 256, 32768 on spokes 483 / 541; 131072 655 / 816), which the index pass
+        // finds out on the GPU: the copy's empty launch costs them 4 us, hence only from 3 x
+        // 2^20 values on.  Fewer fit the caches (150 x 90 x 48, 5000 samples 40.5 / 43.5), and
+        // 2^22 on few tiles (64^2 x 64, 60000, J = 4 87 / 103; 28^2 x 744, 20000 538 / 279; 56^2
+        // x 300, 30000 399 / 209).  Not for fewer than four samples a tile (320^2 x 128,
+        // 20480, J = 4 414 / 427), up to 32 channels (64^2 x 32, 60000 62 / 68, though 256^2 x
+        // 32, 120000 202 / 142) or where y is in tile order already.
         const int64_t vals = a.M * a.nch, tiles = g.ntiles_own;
-        const bool many = tiles >= 256 && a.nch * tiles >= 32768 ? vals >= 1 << 20 : tiles >= 25 && vals >= 1 << 22;
-        sel.grouped = a.M > 0 && (D == 3 || (a.nch > 32 && a.M >= 4 * tiles && many));
+        const bool many = tiles >= 256 && a.nch * tiles >= 32768 ? vals >= 3 << 20 : tiles >= 25 && vals >= 1 << 22;
+        sel.grouped = a.M > 0 && (D == 3 || (a.nch > 32 && a.order && a.M >= 4 * tiles && many));
         return sel;
     }
     if (D == 2 && tcells <= 512 && os_on) {

@@ -274,7 +274,7 @@ struct KbnSpreadArgs {
     const int *otile_order;    // owner tiles by decreasing entry count (coarse)
     const int *swork;          // work items [n][4]: tile, entry begin, entry end, slot (-1: direct)
     const int *scomb;          // multi-item tiles [n][3]: tile, first slot, slots
-    const int *scounts;        // [0] work items, [1] multi-item tiles
+    const int *scounts;        // [0] work items, [1] multi-item tiles, [2] samples along a trajectory
     float2 *partial;           // [smax][nch][prod To] partial tiles of multi-item tiles
     const int *rec_p;          // per owner-list entry: sorted sample position
     const int *rec_q;          // per owner-list entry: the sample's index in y
@@ -311,6 +311,7 @@ struct KbnSpreadSel {
     int tcells = 0;          // cells of an owner tile
     int ngr = 0, ny = 0;     // grid: channel groups x work-item rows
     bool grouped = false;    // matrix-core: values copied in tile order, a group's channels side by side
+                             // (2D: unless the samples come along a trajectory)
 };
 KbnSpreadSel kbn_spread_select(const KbnGeom &g, const KbnSpreadArgs &a);
 struct KbnSpreadJob {

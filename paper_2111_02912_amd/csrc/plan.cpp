@@ -1225,7 +1225,7 @@ int64_t const_bytes(const kbn_plan p) {
         b += block_bytes(4 * c.deap[d]) + block_bytes(8 * c.tw[d]);
     b += block_bytes(4 * c.coef) + block_bytes(4) /*flag*/ + block_bytes(4 * c.toff) +
          block_bytes(4) /*nsub*/ + block_bytes(4 * c.ooff) + block_bytes(4 * c.otile_order) +
-         block_bytes(4 * c.scomb) + block_bytes(8) /*scounts*/;
+         block_bytes(4 * c.scomb) + block_bytes(12) /*scounts*/;
     return b;
 }
 
@@ -1311,7 +1311,7 @@ int kbn_plan_create(kbn_plan *out, int D, const int64_t *N, const kbn_opts *opts
     if (rc == KBN_OK) rc = dev_alloc(p, &p->ooff, cs.ooff, stream);
     if (rc == KBN_OK) rc = dev_alloc(p, &p->otile_order, cs.otile_order, stream);
     if (rc == KBN_OK) rc = dev_alloc(p, &p->scomb, cs.scomb, stream);
-    if (rc == KBN_OK) rc = dev_alloc(p, &p->scounts, 2, stream);
+    if (rc == KBN_OK) rc = dev_alloc(p, &p->scounts, 3, stream);
     if (rc == KBN_OK && (hipEventCreateWithFlags(&p->upload_done, hipEventDisableTiming) != hipSuccess ||
                          hipEventRecord(p->upload_done, stream) != hipSuccess))
         rc = fail(KBN_ERR_HIP, "upload event");

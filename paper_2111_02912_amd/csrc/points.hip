@@ -690,6 +690,19 @@ __device__ __forceinline__ void block_scan3_1024(int x[3], int ex[3], int tot[3]
     lds_barrier();
 }
 
+// Whether the caller's samples come along a trajectory: of up to 1024 neighbours in
+// the sorted order, at least half follow each other in the caller's.  order_step is
+// this thread's pair (its loads are in flight until order_vote, which adds +1 or -1 for
+// it to *votes in LDS: cleared, and read, behind barriers of the caller).
+__device__ __forceinline__ int order_step(const int *__restrict__ order, int64_t M) {
+    const int64_t p = (int64_t)threadIdx.x * (M > 1024 ? (M - 1) / 1024 : 1);
+    return p + 1 < M ? order[p + 1] - order[p] : 0;
+}
+__device__ __forceinline__ void order_vote(int step, int *votes) {
+    const int yes = __popcll(__ballot(step == 1)), no = __popcll(__ballot(step != 0 && step != 1));
+    if ((threadIdx.x & 63) == 0) atomicAdd(votes, yes - no);
+}
+
 // Owner offsets (exclusive scan of the counts, ooff[n] = total), the tiles in
 // decreasing order of entry count, and the spread work items; up to KBN_OWN_LDS
 // tiles in one workgroup, whose counts, offsets and order live in LDS (3 ntiles
@@ -706,20 +719,24 @@ __device__ __forceinline__ void block_scan3_1024(int x[3], int ex[3], int tot[3]
 // doubles until the slots fit in `smax`.  Outputs:
 //   work[i] = (tile, first entry, end entry, slot or -1), counts2[0] = items
 //   comb[k] = (tile, first slot, number of slots),     counts2[1] = tiles
+//   counts2[2] = 1 if the samples (their order sorder) come along a trajectory
 __global__ void __launch_bounds__(1024)
-k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, int *__restrict__ ooff,
-               int *__restrict__ order, int *__restrict__ work, int *__restrict__ comb,
-               int *__restrict__ counts2) {
+k_owner_finish(int ntiles, int seg, int smax, int64_t M, const int *__restrict__ sorder,
+               const int *__restrict__ ocount, int *__restrict__ ooff, int *__restrict__ order,
+               int *__restrict__ work, int *__restrict__ comb, int *__restrict__ counts2) {
     extern __shared__ int lds[];
     __shared__ int wsum[16];
     __shared__ int wsum3[3][16];
-    __shared__ int hist[KBN_OWN_KEYS], start[KBN_OWN_KEYS];
+    __shared__ int hist[KBN_OWN_KEYS], start[KBN_OWN_KEYS], votes;
     const int tid = threadIdx.x;
     const int nr = (ntiles + 1023) / 1024;
     int *off = lds + ntiles, *ord = lds + 2 * ntiles;
+    const int step = order_step(sorder, M);
 #pragma unroll 4
     for (int t = tid; t < ntiles; t += 1024) lds[t] = ocount[t];
+    if (tid == 0) votes = 0;
     lds_barrier();
+    order_vote(step, &votes);
     const int *cnt = lds;
     // offsets
     int carry = 0;
@@ -801,6 +818,7 @@ k_owner_finish(int ntiles, int seg, int smax, const int *__restrict__ ocount, in
     if (tid == 0) {
         counts2[0] = cw;
         counts2[1] = cc;
+        counts2[2] = votes >= 0;
     }
 #pragma unroll 4
     for (int t = tid; t < ntiles; t += 1024) {
@@ -859,11 +877,13 @@ k_owner_spans(int ntiles, int nb, int seg_log, const int *__restrict__ ocount, i
 }
 
 __global__ void __launch_bounds__(1024)
-k_owner_top(int ntiles, int nb, int seg_log, int smax, int *__restrict__ scratch, int *__restrict__ ooff,
-            int *__restrict__ counts2) {
-    __shared__ int wsum[16], lslots[KBN_FIN_LEVELS];
+k_owner_top(int ntiles, int nb, int seg_log, int smax, int64_t M, const int *__restrict__ sorder,
+            int *__restrict__ scratch, int *__restrict__ ooff, int *__restrict__ counts2) {
+    __shared__ int wsum[16], lslots[KBN_FIN_LEVELS], votes;
     const int tid = threadIdx.x;
     const FinScratch f = fin_scratch(scratch, nb);
+    const int step = order_step(sorder, M);
+    if (tid == 0) votes = 0;
     int run = 0, tot;
     for (int b0 = 0; b0 < nb; b0 += 1024) {
         const int v = b0 + tid < nb ? f.sum[b0 + tid] : 0;
@@ -872,6 +892,7 @@ k_owner_top(int ntiles, int nb, int seg_log, int smax, int *__restrict__ scratch
         run += tot;
     }
     if (tid == 0) ooff[ntiles] = run;
+    order_vote(step, &votes);  // (behind the scan's barriers; read behind the next ones)
     for (int l = tid >> 6; l < KBN_FIN_LEVELS; l += 16) {  // one wavefront per level
         int s = 0;
         for (int b = tid & 63; b < nb; b += 64) s += f.slots[l * nb + b];
@@ -897,6 +918,7 @@ k_owner_top(int ntiles, int nb, int seg_log, int smax, int *__restrict__ scratch
             f.head[4] = 0;
             counts2[0] = lslots[level] + ntiles - split;
             counts2[1] = split;
+            counts2[2] = votes >= 0;
         }
         run += tot;
     }
@@ -1105,12 +1127,13 @@ hipError_t kbn_launch_owner_lists(const KbnGeom &g, int64_t M, const int *cell, 
                                s>>>(o, M, cell, frac, toff, ocount);                                   \
         if (n <= KBN_OWN_LDS) {                                                                        \
             k_owner_finish<<<dim3(1), dim3(1024), 3 * sizeof(int) * n, s>>>(                           \
-                n, seg, smax, ocount, ooff, otile_order, swork, scomb, scounts);                       \
+                n, seg, smax, M, order, ocount, ooff, otile_order, swork, scomb, scounts);             \
         } else {                                                                                       \
             const int nb = fin_spans(n);                                                               \
             int *scratch = ocount + n + 1;                                                             \
             k_owner_spans<<<dim3(nb), dim3(1024), 0, s>>>(n, nb, seg_log, ocount, scratch);            \
-            k_owner_top<<<dim3(1), dim3(1024), 0, s>>>(n, nb, seg_log, smax, scratch, ooff, scounts);  \
+            k_owner_top<<<dim3(1), dim3(1024), 0, s>>>(n, nb, seg_log, smax, M, order, scratch, ooff,  \
+                                                       scounts);                                       \
             k_owner_place<<<dim3(nb), dim3(1024), 0, s>>>(n, nb, ocount, scratch, ooff, otile_order,   \
                                                           swork, scomb);                               \
         }                                                                                              \

@@ -88,16 +88,20 @@ def test_matrix_core_spread_of_eight_taps(N, M, nch):
 
 
 # many values: copied in tile order first, on many tiles (256, and 32768 with the
-# channels) from 2^20 of them, on fewer (25) from 2^22, and from 4 samples a tile; groups
-# of 64 channels and a remainder
-@pytest.mark.parametrize("N,M,nch", [((128, 100), 25575, 41), ((128, 100), 25576, 41), ((128, 100), 26300, 40),
-                                     ((128, 100), 16383, 64), ((128, 100), 16384, 65), ((128, 100), 8100, 130),
-                                     ((128, 100), 3199, 330), ((128, 100), 3200, 330), ((40, 36), 20971, 200),
+# channels) from 3 x 2^20 of them, on fewer (25) from 2^22, and from 4 samples a tile;
+# groups of 64 channels and a remainder
+@pytest.mark.parametrize("N,M,nch", [((128, 100), 32767, 96), ((128, 100), 32768, 96), ((128, 100), 24198, 130),
+                                     ((128, 100), 3199, 984), ((128, 100), 3200, 984), ((40, 36), 20971, 200),
                                      ((40, 36), 20972, 200), ((16, 20), 65536, 64), ((20, 20), 65536, 64)])
-def test_matrix_core_spread_of_many_channels(N, M, nch):
+@pytest.mark.parametrize("along", [False, True])
+def test_matrix_core_spread_of_many_channels(N, M, nch, along):
+    """Samples in no order are copied, those along a trajectory are not."""
     from paper_2111_02912_amd.cg import cg_sense
-    print(f"2D spread N={N} of {nch} channels, M={M}", flush=True)
+    print(f"2D spread N={N} of {nch} channels, M={M} along a trajectory: {along}", flush=True)
     om = _samples(M, 2)
+    if along:
+        t = np.linspace(0, 1, M, endpoint=False)
+        om = np.stack([3.1 * t * np.cos(80 * t), 3.1 * t * np.sin(80 * t)], 1).astype(np.float32)
     om[7::11, 0] = np.nan
     y = W.complex_normal((nch, 1, M), 67)
     p = _plan(N, om, "matrix")
